@@ -258,10 +258,10 @@ float reslice_guard(int gram_prec, int inv, int U) {
 
 size_t flags_region(int n_sc) { return ((size_t)n_sc * 4 + 255) & ~size_t(255); }
 
-// The list of subcarriers the split FP64 pass recomputes with one workgroup
-// per cluster (one int per workgroup), at the end of the workspace, and 256
-// bytes before it the word where the kernels mark that they flagged
-// anything.
+// The list of subcarriers that the U = 64 FP64 pass inverts into its slots (one
+// int per slot), at the end of the workspace, and 256 bytes before it the word
+// where the kernels mark that they flagged anything and the word that says
+// whether the slots did not suffice.
 constexpr size_t kList0Room = dbp::kFixMaxSlots * sizeof(int) + 512;
 
 // A fresh value per call for that mark (never 0).
@@ -314,8 +314,8 @@ int setup_reslice(const char* who, dbp::UlArgs& a, dbp::FixArgs& f, int32_t* sta
   bookkeeping(static_cast<char*>(ws), ws_bytes, &f.list0, &a.any);
   a.epoch = next_epoch();
   f.any = a.any;
+  f.more = a.any + 1;
   f.epoch = a.epoch;
-  f.split = 0;
   f.n_slots = slots;
   f.H = a.H;
   f.y = a.y;
@@ -400,7 +400,6 @@ int detect_admm_impl(const char* who, const void* H, const void* y, void* s_hat,
   st = device_status(who, launch_preprocessing(a, U, gram_prec, inv, hs, 0));
   if (st || (!hard && cond == 0.f)) return st;
   fix_params(f, U, rho, gamma, N0, Es, reg, qam, true);
-  f.split = U >= 32;   // large inverses: one workgroup per cluster for each workgroup's first subcarrier
   return device_status(who, dbp::launch_admm_ul_fix64(f, hs));
 }
 
@@ -472,7 +471,6 @@ int dbp_detect_admm_factored(const void* H, const void* factors, const void* y, 
   st = device_status(who, dbp::launch_admm_ul_factored(a, U, a.nw, hs));
   if (st || !hard) return st;
   fix_params(f, U, rho, gamma, N0, Es, reg, qam, true);
-  f.split = U >= 32;
   return device_status(who, dbp::launch_admm_ul_fix64(f, hs));
 }
 
@@ -739,6 +737,7 @@ int dbp_detect_admm_batch(const dbp_frame* frames, int n_frames, int U, void* st
   }
   dbp::UlBatch b{};
   dbp::FixBatch fb{};
+  fb.slot_c = C_max;
   // FP64 slots: in the workspace (after its flags) with the most room
   const size_t slot = dbp::fix64_slot_bytes(U, C_max);
   char* slots = nullptr;

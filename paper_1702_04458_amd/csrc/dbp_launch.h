@@ -59,9 +59,9 @@ struct FixArgs {
   c32* shat;          // [n_sc][n_sym][U]
   uint8_t* hard;      // [n_sc][n_sym][U] or null (the FP64 factor rule without hard decisions)
   int32_t* flags;     // [n_sc] status bits of the FP32 pass (read; the re-slice bit is kept)
-  void* ws;           // n_slots blocks of C U^2 complex FP64 (ADMM), or null (CG)
-  int* list0;         // [n_slots] subcarriers recomputed with one workgroup per cluster (split)
-  int split;          // 1: each workgroup's first subcarrier goes to the per-cluster kernels
+  void* ws;           // n_slots blocks of C U^2 complex FP64 (ADMM, U = 64), or null (CG)
+  int* list0;         // [n_slots] subcarriers inverted into the slots (U = 64)
+  uint32_t* more;     // set to 1 when more than n_slots subcarriers are flagged, else 0 (U = 64)
   int n_sc, n_sym, B, U, C, S, T, reg, L, n_slots;
   const uint32_t* any;   // equals epoch when the FP32 pass flagged any subcarrier of this call
   uint32_t epoch;
@@ -94,6 +94,7 @@ struct UlBatch {
 struct FixBatch {
   FixArgs f[kMaxBatch];
   int n;
+  int slot_c;   // largest C of the frames: a slot holds slot_c U^2 complex values
 };
 static_assert(sizeof(UlBatch) <= 4096 && sizeof(FixBatch) <= 4096, "kernel argument blocks exceed 4 KiB");
 
