@@ -1100,14 +1100,11 @@ __device__ __forceinline__ c32 gram_mfma_u16(const UlArgs& a, c32 (&A)[16], int 
 // accumulated (two MFMAs per four users instead of four).  The operands come
 // from the register copy hcol (lane u of group g: Hu[i][u]) through LDS, so H
 // is read from memory once.  The 16x16 result (lane l: column l%16, rows 4(l/16)+r) goes
-// through the wave's stage buffer so that lane b < 16 of each problem's lane
-// group reads row b.
-// SPLITOUT: the result in the split-row layout of gj_invert_sym_split16 (lane
-// r of DPP row h of the group gets entries 8h .. 8h+7 of row r) instead of
-// one row per lane u < 16.
-template <bool SPLITOUT = false>
-__device__ __forceinline__ void gram_dl_mfma_s16_u32(const c32 (&hcol)[16], c32 (&A)[SPLITOUT ? 8 : 16], int lane,
-                                                     int g, int u, c32* stage) {
+// through the wave's stage buffer.
+// The result is in the split-row layout of gj_invert_sym_split16 (lane r of DPP
+// row h of the group gets entries 8h .. 8h+7 of row r).
+__device__ __forceinline__ void gram_dl_mfma_s16_u32(const c32 (&hcol)[16], c32 (&A)[8], int lane, int g, int u,
+                                                     c32* stage) {
   const int q = lane >> 4, r16 = lane & 15;
   f32x4 re[2], im[2];
 #pragma unroll
@@ -1141,26 +1138,13 @@ __device__ __forceinline__ void gram_dl_mfma_s16_u32(const c32 (&hcol)[16], c32 
   // Re A[b][v] = (P P^T)[b][v] - M[b][v] - M[v][b], Im A[b][v] = M[b][v] - M[v][b]
   const int p = lane >> 5, b = lane & 31;
   const float* stf = reinterpret_cast<const float*>(stage + p * 256);
-  if constexpr (SPLITOUT) {
-    const int r = b & 15, v0 = 8 * (b >> 4);
-    c32 row[8];
-    lds_read_vec<8>(stage + p * 256 + r * 16 + v0, row);
+  const int r = b & 15, v0 = 8 * (b >> 4);
+  c32 row[8];
+  lds_read_vec<8>(stage + p * 256 + r * 16 + v0, row);
 #pragma unroll
-    for (int v = 0; v < 8; ++v) {
-      const float mt = stf[2 * ((v0 + v) * 16 + r) + 1];
-      A[v] = c32{row[v].re - row[v].im - mt, row[v].im - mt};
-    }
-  } else if (b < 16) {
-#pragma unroll
-    for (int v0 = 0; v0 < 16; v0 += 8) {
-      c32 row[8];
-      lds_read_vec<8>(stage + p * 256 + b * 16 + v0, row);
-#pragma unroll
-      for (int v = 0; v < 8; ++v) {
-        const float mt = stf[2 * ((v0 + v) * 16 + b) + 1];
-        A[v0 + v] = c32{row[v].re - row[v].im - mt, row[v].im - mt};
-      }
-    }
+  for (int v = 0; v < 8; ++v) {
+    const float mt = stf[2 * ((v0 + v) * 16 + r) + 1];
+    A[v] = c32{row[v].re - row[v].im - mt, row[v].im - mt};
   }
   wave_lds_sync();
 }
@@ -2060,9 +2044,9 @@ __global__ void __launch_bounds__(512) dcg_ul_f32(UlArgs a) {
   }
 }
 
-// Newton steps of the budgeted (P1) at most (quadratic convergence from
-// below: about four to six steps reach FP32 accuracy).
-constexpr int kBudgetNewton = 12;
+// Inversions of one budgeted (P1) at most (one from a cold start, none to one
+// from the previous x-update's shift, see admm_dl_body).
+constexpr int kBudgetSteps = 12;
 
 // ---------------------------------------------------------------------------
 // Algorithm 3 (decentralized ADMM beamforming, epsilon = 0), S x S branch
@@ -2073,13 +2057,23 @@ constexpr int kBudgetNewton = 12;
 // row a of A_c^{-1}.
 // ---------------------------------------------------------------------------
 // BUDGET: every x-update is the budgeted step (P1) with ||x_c||^2 <= P_c.
-// When the unconstrained step exceeds the budget, x = (H_c^H H_c + tau I)^{-1}
-// H_c^H v with tau > 1/rho the root of ||x(tau)|| = sqrt(P_c) (the Lagrange
-// multiplier of the budget is rho tau - 1): Newton's method on
-// 1/||x(tau)|| - 1/sqrt(P_c), which is concave and increasing in tau, so the
-// iterates from tau = 1/rho rise monotonically to the root (the trust-region
-// update tau += ||x||^2 (||x|| - sqrt(P)) / (sqrt(P) x^H (G + tau I)^{-1} x)).
-// Each step forms the Gram again and inverts the shifted matrix.
+// When the unconstrained step exceeds the budget, x = x(tau) = (H_c^H H_c +
+// tau I)^{-1} H_c^H v with tau > 1/rho the root of ||x(tau)||^2 = P_c (the
+// Lagrange multiplier of the budget is rho tau - 1).  The kernel keeps the
+// inverse M at the shift tau_M of the last inversion (first 1/rho).  For a
+// right-hand side r its powers u_j = M^{j+1} r, j = 0 .. 3, give x at any nearby
+// shift, x(tau_M + d) = sum_j (-d)^j u_j, and through their inner products
+// g_m = r^H M^{m+2} r the squared norm N(d) = sum_m (m + 1) (-d)^m g_m, m <= 6.
+// d is the root of N(d) = P_c: a Halley step on 1/||x|| - 1/sqrt(P_c) (concave
+// and increasing in tau, and nearly linear), polished on the polynomial where
+// the series converges fast.  If the truncated tail of x is below FP32
+// rounding the x-update is done, with no inversion at all; otherwise M is
+// formed anew at tau_M + d and the step repeats.  The shift moves little from
+// one x-update to the next, so a product (about 45 instructions) replaces most
+// inversions (about 900): B=256 U=32 C=16, 1200 subcarriers, T=5, budgets
+// binding on half of the clusters: 754 us with Newton's method and a Gram and
+// an inversion per step (about 25 of them), 240 us in this form (3.7 times at
+// budgets of a third of the mean energy); its error against FP64 is unchanged.
 template <int G, int SG, bool BUDGET = false>
 __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
   constexpr int P = 64 / G;
@@ -2116,24 +2110,25 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
   // only after the inverse, from hcol through LDS, so that it is not live
   // during the Gram and the sweep (register budget of four waves per SIMD).
   constexpr bool LATE_H = (G == 32 && SG == 16);
-  // There (without the budget) A_c and its inverse also take the split-row
-  // layout: lane u holds entries 8 (u / 16) .. + 7 of row u % 16, so that all
-  // 32 lanes of the group share the sweep and the products A_c^{-1} r.
-  constexpr bool ASPLIT = LATE_H && !BUDGET;
-  c32 hcol[SG], hrow[RS], A[ASPLIT ? 8 : SG];
+  // There A_c and its inverse also take the split-row layout: lane u holds
+  // entries 8 (u / 16) .. + 7 of row u % 16, so that all 32 lanes of the group
+  // share the sweep and the products A_c^{-1} r.
+  constexpr bool ASPLIT = LATE_H;
+  constexpr int NR = ASPLIT ? 8 : SG;      // entries of A_c per lane
+  c32 hcol[SG], hrow[RS], A[NR];
 #pragma unroll
   for (int i = 0; i < SG; ++i) hcol[i] = (active && i < S) ? Hk[(size_t)i * sa + (size_t)u * su] : cz();
 #pragma unroll
-  for (int i = 0; i < (ASPLIT ? 8 : SG); ++i) A[i] = cz();
+  for (int i = 0; i < NR; ++i) A[i] = cz();
   if constexpr (!LATE_H) {
 #pragma unroll
     for (int i = 0; i < RS; ++i) hrow[i] = (active && ra < S) ? Hk[(size_t)ra * sa + (size_t)(r0 + i) * su] : cz();
   }
   // The Gram H_c^H H_c, (H_c^H H_c)[a][b] = sum_u conj(Hu[a][u]) Hu[b][u], into
   // M (rows a < S; M must hold zeros).  Every lane of the wave takes part.
-  auto gram_into = [&](c32 (&M)[SG]) {
-    if constexpr (LATE_H) {
-      gram_dl_mfma_s16_u32<false>(hcol, M, lane, g, u, sm.stage + wave * kStageWave);
+  auto gram_into = [&](c32 (&M)[NR]) {
+    if constexpr (ASPLIT) {
+      gram_dl_mfma_s16_u32(hcol, M, lane, g, u, sm.stage + wave * kStageWave);
     } else {
       // Row b of Hu_c is broadcast from the stage buffer of this wave.
       c32* stage = sm.stage + wave * kStageWave;
@@ -2163,20 +2158,30 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
   };
   // A_c = H_c^H H_c + rho^{-1} I_S
   const float irho = 1.0f / a.rho;
-  if constexpr (ASPLIT) {
-    gram_dl_mfma_s16_u32<true>(hcol, A, lane, g, u, sm.stage + wave * kStageWave);
-    const int h = u >> 4, r = u & 15;
+  // M holds H_c^H H_c; leaves (H_c^H H_c + tau I)^{-1} (identity past S)
+  auto shift_invert = [&](c32 (&M)[NR], float tau) {
+    if constexpr (ASPLIT) {
+      const int h = u >> 4, r = u & 15;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (8 * h + i == r) A[i].re += (r < S) ? irho : 1.0f;
-    gj_invert_sym_split16(A, r, h, line + gbase);
-  } else {
-    gram_into(A);
+      for (int i = 0; i < 8; ++i)
+        if (8 * h + i == r) M[i].re += (r < S) ? tau : 1.0f;
+      gj_invert_sym_split16(M, r, h, line + gbase);
+    } else {
 #pragma unroll
-    for (int v = 0; v < SG; ++v)
-      if (v == u) A[v].re += (u < S) ? irho : 1.0f;
-    gj_invert<SG>(A, u, line, gbase);
+      for (int v = 0; v < SG; ++v)
+        if (v == u) M[v].re += (u < S) ? tau : 1.0f;
+      gj_invert<SG>(M, u, line, gbase);
+    }
+  };
+  gram_into(A);
+  // the budgeted step inverts the Gram again at other shifts
+  constexpr bool KEEP = BUDGET && ASPLIT;
+  c32 gk[KEEP ? 8 : 1];
+  if constexpr (KEEP) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) gk[i] = A[i];
   }
+  shift_invert(A, irho);
   if constexpr (LATE_H) {
     // Transpose the S x G tile of each problem through the wave's stage
     // buffer, one problem at a time: entry (i, w) at i (G + 2) + w.  The
@@ -2202,6 +2207,19 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
       }
       wave_lds_sync();
     }
+  }
+
+  c32 Mt[BUDGET ? NR : 1];   // inverse at the shift tauM
+  float tauM = irho;
+  if constexpr (BUDGET) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i) Mt[i] = A[i];
+  }
+  if constexpr (KEEP) {
+    // the Gram's rows wait in the wave's stage buffer, which is free from here
+    // on with the split rows (lane-private slots)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sm.stage[wave * kStageWave + i * 64 + lane] = gk[i];
   }
 
   // Broadcast line of the iterations, in the wave's stage buffer (free once
@@ -2274,33 +2292,62 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
       if constexpr (BUDGET) {
         // padding cluster slots carry no budget
         const float Pc = active ? a.P[c] : 0.f;
-        const float e = group_sum<G>((u < S) ? xa.re * xa.re + xa.im * xa.im : 0.f);
-        const bool need = active && e > Pc;
-        if (__ballot(need)) {   // wave-uniform: the Gram and sweep below are wave operations
-          const float sp = sqrtf(Pc);
-          float tau = irho, et = e;
-          c32 xn = xa;
-          for (int it = 0; it < kBudgetNewton; ++it) {
-            c32 Mt[SG];
-#pragma unroll
-            for (int v = 0; v < SG; ++v) Mt[v] = cz();
-            gram_into(Mt);
-#pragma unroll
-            for (int v = 0; v < SG; ++v)
-              if (v == u) Mt[v].re += (u < S) ? tau : 1.0f;
-            gj_invert<SG>(Mt, u, line, gbase);
-            xn = group_matvec<SG>(Mt, r, u, line, gbase);
-            const c32 mx = group_matvec<SG>(Mt, xn, u, line, gbase);
-            et = group_sum<G>((u < S) ? xn.re * xn.re + xn.im * xn.im : 0.f);
-            const float w2 = group_sum<G>((u < S) ? xn.re * mx.re + xn.im * mx.im : 0.f);
-            const float sq = sqrtf(et);
-            const bool go = need && sq - sp > 1e-6f * sp && w2 > 0.f;
-            if (go) tau += et * (sq - sp) / (sp * w2);
-            if (!__ballot(go)) break;
+        auto dot = [&](c32 p, c32 q) -> float {
+          const float d = fmaf(p.re, q.re, p.im * q.im);
+          if constexpr (ASPLIT) return group_sum<16>(d);   // both rows of 16 lanes hold every entry
+          return group_sum<G>((u < S) ? d : 0.f);
+        };
+        auto mul = [&](c32 q) -> c32 {
+          if constexpr (ASPLIT) return matvec_split16(Mt, q);
+          else return group_matvec<SG>(Mt, q, u, line, gbase);
+        };
+        bool need = active && dot(xa, xa) > Pc;
+        const float sp = sqrtf(Pc);
+        for (int it = 0; __ballot(need); ++it) {   // wave-uniform: products and inversions are wave operations
+          const c32 u0 = mul(r), u1 = mul(u0), u2 = mul(u1), u3 = mul(u2);
+          const float g0 = dot(u0, u0), g1 = dot(u0, u1), g2 = dot(u1, u1), g3 = dot(u1, u2), g4 = dot(u2, u2),
+                      g5 = dot(u2, u3), g6 = dot(u3, u3);
+          // Halley's step, at most twice Newton's
+          const float q = sqrtf(g0) / sp - 1.0f;
+          float d = 2.f * q * g0 * g1 / fmaxf(g1 * g1, fmaf(3.f * q, fmaf(g1, g1, -g0 * g2), 2.f * g1 * g1));
+          d = fmaxf(d, irho - tauM);
+          const float lam = sqrtf(g6 / g4);   // rate of the series (at most the largest eigenvalue of M)
+          if (fabsf(d) * lam < 0.3f) {
+            // Newton on the polynomial N(d)
+#pragma unroll 1
+            for (int j = 0; j < 3; ++j) {
+              const float e = -d;
+              const float N = fmaf(e, fmaf(e, fmaf(e, fmaf(e, fmaf(e, fmaf(e, 7.f * g6, 6.f * g5), 5.f * g4), 4.f * g3),
+                                           3.f * g2), 2.f * g1), g0);
+              const float D = fmaf(e, fmaf(e, fmaf(e, fmaf(e, fmaf(e, 42.f * g6, 30.f * g5), 20.f * g4), 12.f * g3),
+                                           6.f * g2), 2.f * g1);   // -dN / dd
+              d = fmaxf(fmaf(2.f * N, (sqrtf(N) / sp - 1.0f) / D, d), irho - tauM);
+            }
           }
-          // the last iterate lies on the budget up to rounding; a final
-          // scale keeps it feasible
-          if (need) xa = (et > Pc) ? cscale(xn, sqrtf(Pc / et)) : xn;
+          const float d2 = d * d;
+          c32 xn = c32{fmaf(-d, u1.re, u0.re), fmaf(-d, u1.im, u0.im)};
+          xn = c32{fmaf(d2, fmaf(-d, u3.re, u2.re), xn.re), fmaf(d2, fmaf(-d, u3.im, u2.im), xn.im)};
+          const float e = dot(xn, xn);
+          // the tail of the series, about d^4 ||u_3|| lam, below half a unit of FP32 rounding
+          const bool last = it >= kBudgetSteps;
+          const bool done = last || d2 * d2 * sqrtf(g6) * lam <= 3e-8f * sp;
+          if (need && done) {
+            // on the budget up to rounding; a final scale keeps it feasible
+            xa = (e > Pc) ? cscale(xn, sqrtf(Pc / e)) : xn;
+            need = false;
+          }
+          if (!__ballot(need)) break;
+          // (a problem that is done or below its budget inverts at its old shift again)
+          if (need) tauM += d;
+          if constexpr (KEEP) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) Mt[i] = sm.stage[wave * kStageWave + i * 64 + lane];
+          } else {
+#pragma unroll
+            for (int i = 0; i < NR; ++i) Mt[i] = cz();
+            gram_into(Mt);
+          }
+          shift_invert(Mt, tauM);
         }
       }
       return xa;
@@ -2562,7 +2609,8 @@ static hipError_t launch_dl(const DlArgs& a, int U, int nw, hipStream_t st) {
     case 32:
       if (S <= 8) return launch(admm_dl_f32<32, 8, BUDGET>, a, nw, st);
       if (S <= 16) {
-        // the budgeted form keeps a second S x S matrix live: no 128-register cap
+        // the budgeted form keeps a second inverse live (176 registers): capped at
+        // 128 it spills 152 of them (240 -> 293 us at B=256 C=16, 1200 subcarriers)
         if constexpr (BUDGET) return launch(admm_dl_f32<32, 16, true>, a, nw, st);
         return launch(admm_dl_f32_w4<32, 16>, a, nw, st);
       }
