@@ -290,7 +290,7 @@ __device__ __forceinline__ c32 matvec16(const c32 (&A)[16], c32 q) {
   DBP_MV16_BLOCK(12, 13, 14, 15);
   return cadd(a0, a1);
 }
-// The same with conjugated matrix entries: acc = sum_v conj(A[v]) * q_v.
+// The same with conjugated matrix entries: acc = sum_v conj(A[OFF + v]) * q_v.
 #define DBP_MV16C_BLOCK(V0, V1, V2, V3)                                                    \
   asm volatile(                                                                          \
       "s_nop 1\n\t"                                                                      \
@@ -312,8 +312,8 @@ __device__ __forceinline__ c32 matvec16(const c32 (&A)[16], c32 q) {
       "v_fmac_f32_dpp %3, -%4, %13 row_newbcast:" #V3 " row_mask:0xf bank_mask:0xf\n\t"  \
       "s_nop 1"                                                                          \
       : "+v"(a0.re), "+v"(a0.im), "+v"(a1.re), "+v"(a1.im)                               \
-      : "v"(q.re), "v"(q.im), "v"(A[V0].re), "v"(A[V0].im), "v"(A[V1].re), "v"(A[V1].im), \
-        "v"(A[V2].re), "v"(A[V2].im), "v"(A[V3].re), "v"(A[V3].im))
+      : "v"(q.re), "v"(q.im), "v"(A[OFF + V0].re), "v"(A[OFF + V0].im), "v"(A[OFF + V1].re), "v"(A[OFF + V1].im), \
+        "v"(A[OFF + V2].re), "v"(A[OFF + V2].im), "v"(A[OFF + V3].re), "v"(A[OFF + V3].im))
 #define DBP_MV16C_FIRST(V0, V1, V2, V3)                                                    \
   asm volatile(                                                                          \
       "s_nop 1\n\t"                                                                      \
@@ -335,10 +335,11 @@ __device__ __forceinline__ c32 matvec16(const c32 (&A)[16], c32 q) {
       "v_fmac_f32_dpp %3, -%4, %13 row_newbcast:" #V3 " row_mask:0xf bank_mask:0xf\n\t"  \
       "s_nop 1"                                                                          \
       : "=&v"(a0.re), "=&v"(a0.im), "=&v"(a1.re), "=&v"(a1.im)                               \
-      : "v"(q.re), "v"(q.im), "v"(A[V0].re), "v"(A[V0].im), "v"(A[V1].re), "v"(A[V1].im), \
-        "v"(A[V2].re), "v"(A[V2].im), "v"(A[V3].re), "v"(A[V3].im))
+      : "v"(q.re), "v"(q.im), "v"(A[OFF + V0].re), "v"(A[OFF + V0].im), "v"(A[OFF + V1].re), "v"(A[OFF + V1].im), \
+        "v"(A[OFF + V2].re), "v"(A[OFF + V2].im), "v"(A[OFF + V3].re), "v"(A[OFF + V3].im))
 
-__device__ __forceinline__ c32 matvec16c(const c32 (&A)[16], c32 q) {
+template <int OFF = 0, int N>
+__device__ __forceinline__ c32 matvec16c(const c32 (&A)[N], c32 q) {
   c32 a0, a1;
   DBP_MV16C_FIRST(0, 1, 2, 3);
   DBP_MV16C_BLOCK(4, 5, 6, 7);

@@ -233,14 +233,9 @@ __device__ __forceinline__ void gj_unscale_u32(f32x16& re, f32x16& im, float pvv
 }
 
 // ADD_RHO: add rho to the diagonal first (false: the caller's accumulators
-// already hold G + rho I).  LAZY: leave the swept matrix S with its scales
-// (B^{-1}_ij = -S_ij pv_i pv_j) and return in pvs[0] the reciprocal pivot of
-// this lane's own row (problem l / 32, row l % 32); the diagonal is also not
-// negated at its pivot, so that S_ii ends 2 d_i above the negated form's
-// (no later update reads it) and B^{-1}_ii = -S_ii pv_i^2 + 2 pv_i.
-template <bool ADD_RHO = true, bool LAZY = false>
-__device__ __forceinline__ void gj_invert_mfma_u32(f32x16 (&re)[2], f32x16 (&im)[2], int lane, float rho, float* line,
-                                                   float* pvs = nullptr) {
+// already hold G + rho I).
+template <bool ADD_RHO = true>
+__device__ __forceinline__ void gj_invert_mfma_u32(f32x16 (&re)[2], f32x16 (&im)[2], int lane, float rho, float* line) {
   const int h = lane >> 5, col = lane & 31;
   if constexpr (ADD_RHO) {
 #pragma unroll
@@ -278,29 +273,17 @@ __device__ __forceinline__ void gj_invert_mfma_u32(f32x16 (&re)[2], f32x16 (&im)
       // Re: -pv (Re_i Re_j + Im_i Im_j), Im: -pv (Re_i Im_j - Im_i Re_j)
       const float Are = -pv * first;
       const float Aim = Are;
-      if constexpr (!LAZY) re[p][rr] = dg ? -sr : sr;
+      re[p][rr] = dg ? -sr : sr;
       re[p] = __builtin_amdgcn_mfma_f32_32x32x2f32(Are, first, re[p], 0, 0, 0);
       im[p] = __builtin_amdgcn_mfma_f32_32x32x2f32(Aim, second, im[p], 0, 0, 0);
-      if constexpr (LAZY) {
-        // the pivot reciprocals go to LDS (no vector instruction per pivot)
-        if (lane == 0) line[32 * p + k] = pv;
-      } else {
-        pvv[p] = isk ? pv : pvv[p];
-        // select in place (otherwise the compiler keeps every pivot's pv live
-        // until the end)
-        asm volatile("" : "+v"(pvv[p]));
-      }
+      pvv[p] = isk ? pv : pvv[p];
+      // select in place (otherwise the compiler keeps every pivot's pv live
+      // until the end)
+      asm volatile("" : "+v"(pvv[p]));
     }
   }
-  if constexpr (LAZY) {
-    wave_lds_sync();
-    pvs[0] = line[32 * h + col];   // pv of this lane's own row (problem h, row col)
-    wave_lds_sync();
-    __builtin_amdgcn_sched_barrier(0);
-  } else {
 #pragma unroll
-    for (int p = 0; p < 2; ++p) gj_unscale_u32(re[p], im[p], pvv[p], 1.f, lane, line);
-  }
+  for (int p = 0; p < 2; ++p) gj_unscale_u32(re[p], im[p], pvv[p], 1.f, lane, line);
 }
 
 // Exchange between the wave's two 32-lane halves: v_permlane32_swap(X, Y)
@@ -345,15 +328,13 @@ __device__ __forceinline__ float pair_sum(float v) {
 // accumulators are replaced by (G + rho I)^{-1} on the matrix cores first.
 // One exchange between lanes l and l^32 then gives every lane the full row of
 // its own problem (lane-row layout, problem = l/32).  Returns row u of
-// H_c^H y_c for symbol 0.  LAZY (with INVERT): A receives row u of the swept
-// matrix S with its scales left in place, and *pvl the reciprocal pivot pv_u
-// of this lane's row, so that B^{-1} q = -pv_u sum_v S_uv (pv_v q_v).
+// H_c^H y_c for symbol 0.
 // PACK (factor-only kernel): when a.H16 is set, H is also written as the
 // packed FP16 channel (a.H16, a.hscale; the format of pack_h16, bit for bit):
 // the tile maxima are taken during the Gram's pass and one more pass converts.
-template <bool INVERT, bool LAZY = false, bool FLAT = false, bool PACK = false>
+template <bool INVERT, bool PACK = false>
 __device__ __forceinline__ c32 gram_mfma_u32(const UlArgs& a, c32 (&A)[32], int lane, int wave, float* line,
-                                             float* stage, float* pvl = nullptr) {
+                                             float* stage) {
   const int h = lane >> 5, col = lane & 31;
   f32x16 re[2], im[2];
   c32 hyp[2];
@@ -420,13 +401,13 @@ __device__ __forceinline__ c32 gram_mfma_u32(const UlArgs& a, c32 (&A)[32], int 
       }
     }
   };
-  // the two buffers in turn (no copies).  FLAT: the loop body always runs
+  // the two buffers in turn (no copies).  INVERT: the loop body always runs
   // both halves and the rows past the last full double step follow it (with
   // an exit between the halves the compiler copies the accumulators of the
-  // factor-only kernel on every step; the other kernels are compiled best
-  // with the exit)
+  // factor-only kernel on every step; the CG kernel is compiled best with the
+  // exit)
   fetch(0, hv, yv);
-  if constexpr (FLAT) {
+  if constexpr (INVERT) {
     int s0 = 0;
     for (; s0 + 4 * CH <= a.S; s0 += 4 * CH) {
       fetch(s0 + 2 * CH, hn, yn);
@@ -504,11 +485,7 @@ __device__ __forceinline__ c32 gram_mfma_u32(const UlArgs& a, c32 (&A)[32], int 
     }
     wave_lds_sync();
   }
-  if constexpr (INVERT && LAZY) {
-    gj_invert_mfma_u32<false, true>(re, im, lane, a.rho, line, pvl);
-  } else if constexpr (INVERT) {
-    gj_invert_mfma_u32<false>(re, im, lane, a.rho, line);
-  }
+  if constexpr (INVERT) gj_invert_mfma_u32<false>(re, im, lane, a.rho, line);
   // exchange halves: lanes < 32 keep problem 0, lanes >= 32 keep problem 1
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
@@ -865,6 +842,18 @@ __device__ __forceinline__ c32 gram_inv_mixed_u32(const UlArgs& a, c32 (&A)[32],
   return combine_hy(hyp, h);
 }
 
+// Sums over the four lane groups of v0 .. v3, handed to lane groups 0 .. 3:
+// v_permlane16_swap of (0, 1) and (2, 3) adds rows in pairs, v_permlane32_swap
+// then adds the halves.
+__device__ __forceinline__ float scatter_sum(float v0, float v1, float v2, float v3) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v2), __float_as_uint(v3), false, false);
+  const float s01 = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const float s23 = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(s01), __float_as_uint(s23), false, false);
+  return __uint_as_float(c[0]) + __uint_as_float(c[1]);
+}
+
 // Gram matrices of the four problems of a wave for U = 16 (P = 4) on the
 // matrix cores with v_mfma_f32_16x16x4f32, K running over quadruples of
 // antenna rows: lane l supplies H[s0 + l/16][l%16] (or P = Hr + Hi) as both
@@ -1077,20 +1066,274 @@ __device__ __forceinline__ c32 gram_mfma_u16(const UlArgs& a, c32 (&A)[16], int 
       wave_lds_sync();
     }
   }
-  // H_c^H y_c: sum the four row classes (lanes col, col+16, col+32, col+48)
-  // and hand problem p's sum to row p: v_permlane16_swap of problems (0, 1)
-  // and (2, 3) adds rows in pairs (problem 0 or 2 on even rows, 1 or 3 on odd
-  // rows), v_permlane32_swap then adds the halves, leaving problem q on row q.
-  auto scatter_sum = [](float v0, float v1, float v2, float v3) {
-    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
-    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v2), __float_as_uint(v3), false, false);
-    const float s01 = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-    const float s23 = __uint_as_float(b[0]) + __uint_as_float(b[1]);
-    const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(s01), __float_as_uint(s23), false, false);
-    return __uint_as_float(c[0]) + __uint_as_float(c[1]);
-  };
+  // H_c^H y_c: the sum over the four row classes, problem p's to lane group p
   return c32{scatter_sum(hyp[0].re, hyp[1].re, hyp[2].re, hyp[3].re),
              scatter_sum(hyp[0].im, hyp[1].im, hyp[2].im, hyp[3].im)};
+}
+
+// ---------------------------------------------------------------------------
+// U = 32, one-shot ADMM: the regularised Gram B in 16 x 16 blocks
+//   B = [P Q; Q^H R],  Pi = P^{-1},  W = Pi Q,  Si = (R - Q^H W)^{-1},  X = W Si,
+// applied without forming the rest of the inverse:
+//   t = q_2 - W^H q_1,   B^{-1} q = [Pi q_1 - X t; Si t],
+// which takes the multiply-adds of one 32 x 32 product.  On this hardware FP32
+// matrix instructions do not run beside the vector units, so their time adds
+// to the vector time, and the full 32 x 32 sweep was two thirds of the
+// kernel: 128 of its 192 v_mfma_f32_32x32x2f32 (72 cycles each).  The blocks
+// take 64 v_mfma_f32_16x16x1f32 (both problems' 16-pivot sweeps at once) and
+// 96 v_mfma_f32_16x16x4f32 (33 cycles each) instead, and the Gram skips the
+// block below the diagonal.
+// Every product is of the form X^H Y, for which a lane's accumulator registers
+// are its operands: lane 16 q + c holds X[4 q + r][c] and Y[4 q + r][c], and step
+// r of the product takes rows 4 q + r, q = 0 .. 3, as its four K slots.
+// ---------------------------------------------------------------------------
+struct Tile16 {
+  f32x4 re, im;
+};
+
+// C + sgn X^H Y (SUB: sgn = -1)
+template <bool SUB>
+__device__ __forceinline__ Tile16 tile_mul(const Tile16& X, const Tile16& Y, Tile16 C) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float xr = SUB ? -X.re[r] : X.re[r], xi = SUB ? -X.im[r] : X.im[r];
+    C.re = __builtin_amdgcn_mfma_f32_16x16x4f32(xr, Y.re[r], C.re, 0, 0, 0);
+    C.im = __builtin_amdgcn_mfma_f32_16x16x4f32(xr, Y.im[r], C.im, 0, 0, 0);
+    C.re = __builtin_amdgcn_mfma_f32_16x16x4f32(xi, Y.im[r], C.re, 0, 0, 0);
+    C.im = __builtin_amdgcn_mfma_f32_16x16x4f32(-xi, Y.re[r], C.im, 0, 0, 0);
+  }
+  return C;
+}
+
+// Inverses of the Hermitian positive definite 16 x 16 matrices T[0], T[1] (one of
+// each problem of the wave): the sweep of gj_invert_mfma_u16 with the four blocks
+// of v_mfma_f32_16x16x1f32 holding (Re T[0], Im T[0], Re T[1], Im T[1]).  Row k
+// reaches the lane groups through wave-private LDS (lds: 256 floats).
+__device__ __forceinline__ void tile_invert_pair(Tile16 (&T)[2], int lane, float* lds) {
+  const int q = lane >> 4, col = lane & 15;
+  const bool odd = q & 1;   // this lane group is an imaginary block
+  f32x16 s;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    s[r] = T[0].re[r];
+    s[4 + r] = T[0].im[r];
+    s[8 + r] = T[1].re[r];
+    s[12 + r] = T[1].im[r];
+  }
+  float pvm = 0.f;
+  float* wq = lds + 64 * q + col;                      // write: [lane group][block][column]
+  const float* rq = lds + 16 * (q & 2) + col;          // read: real block of this lane group's problem
+  const float* dq = lds + 16 * (q & 2);
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int g = k >> 2, rr = k & 3;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) wq[16 * b] = s[4 * b + rr];
+    wave_lds_sync();
+    const float w_re = rq[64 * g], w_im = rq[64 * g + 16], d = dq[64 * g + k];
+    wave_lds_sync();
+    const float pv = __builtin_amdgcn_rcpf(d);
+    const bool isk = (col == k);
+    const float wr = isk ? 0.f : w_re, wi = isk ? 0.f : w_im;
+    const float ar = -pv * wr, ai = -pv * wi;
+    // Re: -pv (wr_i wr_j + wi_i wi_j), Im: -pv (wr_i wi_j - wi_i wr_j)
+    s = __builtin_amdgcn_mfma_f32_16x16x1f32(ar, odd ? wi : wr, s, 0, 0, 0);
+    s = __builtin_amdgcn_mfma_f32_16x16x1f32(ai, odd ? -wr : wi, s, 0, 0, 0);
+    pvm = isk ? pv : pvm;
+    asm volatile("" : "+v"(pvm));   // (otherwise every pivot's pv stays live until the end)
+  }
+  // T^{-1} = 2 D - D S D, D = diag(pv)
+  if (!odd) lds[16 * (q >> 1) + col] = pvm;
+  wave_lds_sync();
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const float pc = lds[16 * p + col];
+    const float4 v = *reinterpret_cast<const float4*>(lds + 16 * p + 4 * q);
+    const float pr[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float sc = -pc * pr[r], dg = (4 * q + r == col) ? 2.f * pc : 0.f;
+      T[p].re[r] = fmaf(sc, s[8 * p + r], dg);
+      T[p].im[r] = sc * s[8 * p + 4 + r];
+    }
+  }
+  wave_lds_sync();
+}
+
+// Registers v[m] of lane groups q -> registers v[q] of lane groups m (a 4 x 4
+// transpose of register index and lane group).
+__device__ __forceinline__ void transpose_groups(float (&v)[4]) {
+  const f32pair a = swap_halves(v[0], v[2]), b = swap_halves(v[1], v[3]);
+  const auto lo = __builtin_amdgcn_permlane16_swap(__float_as_uint(a.lo), __float_as_uint(b.lo), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__float_as_uint(a.hi), __float_as_uint(b.hi), false, false);
+  v[0] = __uint_as_float(lo[0]);
+  v[1] = __uint_as_float(lo[1]);
+  v[2] = __uint_as_float(hi[0]);
+  v[3] = __uint_as_float(hi[1]);
+}
+
+// Gram and block factors of the two problems of a wave.  Lane 32 p + 16 h + u
+// receives in A[0 .. 15] column u of Pi (h = 0) or W (h = 1) of problem p and in
+// A[16 .. 31] column u of X^H (h = 0) or Si (h = 1): conjugated, the rows that
+// block_matvec_u32 needs.  Returns entry 16 h + u of H_c^H y_c for symbol 0.
+__device__ __forceinline__ c32 gram_blocks_u32(const UlArgs& a, c32 (&A)[32], int lane, int wave, float* stage) {
+  const int q = lane >> 4, col = lane & 15;
+  // P^T P (P = Hr + Hi) of the blocks (0, 0), (0, 1), (1, 1) and M = Hr^T Hi of
+  // all four; the real diagonal starts from rho
+  f32x4 pp[2][3], mm[2][4];
+  c32 hyp[2][2];
+  const c32* Hp[2];
+  const c32* yp[2];
+  bool act[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const int lp = wave * 2 + p;
+    const int ls = lp / a.Cp, c = lp % a.Cp;
+    const int k = a.blk * a.sc_per_block + ls;
+    act[p] = (k < a.n_sc) && (c < a.C);
+    Hp[p] = act[p] ? a.H + (size_t)k * a.B * 32 + (size_t)c * a.S * 32 : a.H;
+    yp[p] = act[p] ? a.y + (size_t)k * a.n_sym * a.B + (size_t)c * a.S : a.y;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) pp[p][0][r] = pp[p][2][r] = (4 * q + r == col) ? a.rho : 0.f;
+    pp[p][1] = f32x4{};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) mm[p][t] = f32x4{};
+    hyp[p][0] = hyp[p][1] = cz();
+  }
+  // buffer loads over each problem's S rows (as in gram_mfma_u32): row s,
+  // columns col and 16 + col at bytes 256 s + 8 col (+ 128)
+  __amdgpu_buffer_rsrc_t hrs[2], yrs[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    hrs[p] = __builtin_amdgcn_make_buffer_rsrc(const_cast<c32*>(Hp[p]), 0, act[p] ? a.S * 256 : 0, kBufferWord3);
+    yrs[p] = __builtin_amdgcn_make_buffer_rsrc(const_cast<c32*>(yp[p]), 0, act[p] ? a.S * 8 : 0, kBufferWord3);
+  }
+  struct Rows {
+    c32 h[2][2], y[2];   // [problem][column block], four rows (one per lane group)
+  };
+  auto fetch = [&](int s0, Rows& d) {
+    const int s = s0 + q;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      d.h[p][0] = __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(hrs[p], s * 256 + col * 8, 0, 0));
+      d.h[p][1] = __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(hrs[p], s * 256 + 128 + col * 8, 0, 0));
+      d.y[p] = __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(yrs[p], s * 8, 0, 0));
+    }
+  };
+  auto accumulate = [&](const Rows& d) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const c32 x0 = d.h[p][0], x1 = d.h[p][1];
+      const float s0 = x0.re + x0.im, s1 = x1.re + x1.im;
+      pp[p][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(s0, s0, pp[p][0], 0, 0, 0);
+      pp[p][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(s0, s1, pp[p][1], 0, 0, 0);
+      pp[p][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(s1, s1, pp[p][2], 0, 0, 0);
+      mm[p][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x0.re, x0.im, mm[p][0], 0, 0, 0);
+      mm[p][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x0.re, x1.im, mm[p][1], 0, 0, 0);
+      mm[p][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(x1.re, x0.im, mm[p][2], 0, 0, 0);
+      mm[p][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(x1.re, x1.im, mm[p][3], 0, 0, 0);
+      cmacc(hyp[p][0], x0, d.y[p]);
+      cmacc(hyp[p][1], x1, d.y[p]);
+    }
+  };
+  // three buffers in turn: the loads of the next eight rows are in flight
+  Rows d0, d1, d2;
+  fetch(0, d0);
+  fetch(4, d1);
+  for (int s0 = 0; s0 < a.S; s0 += 12) {
+    fetch(s0 + 8, d2);    // zeros past S
+    accumulate(d0);
+    fetch(s0 + 12, d0);
+    accumulate(d1);
+    fetch(s0 + 16, d1);
+    accumulate(d2);
+  }
+  // Re G_IJ = (P^T P)_IJ - M_IJ - (M_JI)^T, Im G_IJ = M_IJ - (M_JI)^T: the
+  // transposes of M_00, M_10 and M_11 through the stage buffer (row pitch 17)
+  Tile16 P[2], Q[2], R[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    constexpr int src[3] = {0, 2, 3};
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) stage[(16 * t + 4 * q + r) * 17 + col] = mm[p][src[t]][r];
+    wave_lds_sync();
+    f32x4 mt[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mt[t][r] = stage[(16 * t + col) * 17 + 4 * q + r];
+    wave_lds_sync();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      P[p].re[r] = pp[p][0][r] - (mm[p][0][r] + mt[0][r]);
+      P[p].im[r] = mm[p][0][r] - mt[0][r];
+      Q[p].re[r] = pp[p][1][r] - (mm[p][1][r] + mt[1][r]);
+      Q[p].im[r] = mm[p][1][r] - mt[1][r];
+      R[p].re[r] = pp[p][2][r] - (mm[p][3][r] + mt[2][r]);
+      R[p].im[r] = mm[p][3][r] - mt[2][r];
+    }
+  }
+  tile_invert_pair(P, lane, stage);   // Pi (Hermitian: Pi^H Q = Pi Q)
+  Tile16 W[2], V[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    W[p] = tile_mul<false>(P[p], Q[p], Tile16{});
+    R[p] = tile_mul<true>(Q[p], W[p], R[p]);
+  }
+  // V = W^H, for X^H = Si W^H
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      stage[(4 * q + r) * 17 + col] = W[p].re[r];
+      stage[(16 + 4 * q + r) * 17 + col] = W[p].im[r];
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      V[p].re[r] = stage[col * 17 + 4 * q + r];
+      V[p].im[r] = -stage[(16 + col) * 17 + 4 * q + r];
+    }
+    wave_lds_sync();
+  }
+  tile_invert_pair(R, lane, stage);   // Si
+  Tile16 X[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) X[p] = tile_mul<false>(R[p], V[p], Tile16{});
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float l_re[4] = {P[0].re[r], W[0].re[r], P[1].re[r], W[1].re[r]};
+    float l_im[4] = {P[0].im[r], W[0].im[r], P[1].im[r], W[1].im[r]};
+    float h_re[4] = {X[0].re[r], R[0].re[r], X[1].re[r], R[1].re[r]};
+    float h_im[4] = {X[0].im[r], R[0].im[r], X[1].im[r], R[1].im[r]};
+    transpose_groups(l_re);
+    transpose_groups(l_im);
+    transpose_groups(h_re);
+    transpose_groups(h_im);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      A[4 * g + r] = c32{l_re[g], l_im[g]};
+      A[16 + 4 * g + r] = c32{h_re[g], h_im[g]};
+    }
+  }
+  return c32{scatter_sum(hyp[0][0].re, hyp[0][1].re, hyp[1][0].re, hyp[1][1].re),
+             scatter_sum(hyp[0][0].im, hyp[0][1].im, hyp[1][0].im, hyp[1][1].im)};
+}
+
+// B^{-1} q from the blocks of gram_blocks_u32, q by entry u = 16 h + (lane % 16)
+// of the problem's 32 lanes.  q_1 (and then t) reaches both rows of 16 lanes by
+// v_permlane16_swap and the multiply-adds by row broadcasts: no LDS.
+__device__ __forceinline__ c32 block_matvec_u32(const c32 (&A)[32], c32 q, bool upper) {
+  auto dup = [](float v, int row) {
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(s[row]);
+  };
+  const c32 a = matvec16c<0>(A, c32{dup(q.re, 0), dup(q.im, 0)});     // Pi q_1 | W^H q_1
+  const c32 t = csub(q, a);                                           // (lower rows) q_2 - W^H q_1
+  const c32 b = matvec16c<16>(A, c32{dup(t.re, 1), dup(t.im, 1)});    // X t | Si t
+  return upper ? csub(a, b) : b;
 }
 
 // Downlink S x S Gram A_c[a][b] = sum_u conj(Hu[a][u]) Hu[b][u] (S <= 16,
@@ -1681,6 +1924,7 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
   constexpr int P = 64 / G;
   constexpr bool RESIDENT = (STAGE == 2 || STAGE == 3);   // iterations against stored factors
   constexpr bool FACTOR = (STAGE == 1 || STAGE == 4);     // preprocessing only
+  constexpr bool BLOCKS = (G == 32 && HALF == 0 && STAGE == 0);   // the inverse as 16 x 16 block factors
   extern __shared__ float4 smem_raw[];
   const int nw = blockDim.x >> 6;
   Smem sm = carve(reinterpret_cast<c32*>(smem_raw), nw);
@@ -1699,17 +1943,17 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
   c32 A[G];
   // (the U = 16 Gram and the U = 32 factor staging write every entry of every
   // lane's row: no clearing)
-  if constexpr (!(G == 16 && !RESIDENT) && !(G == 32 && RESIDENT)) {
+  if constexpr (!(G == 16 && !RESIDENT) && !(G == 32 && RESIDENT) && !BLOCKS) {
 #pragma unroll
     for (int v = 0; v < G; ++v) A[v] = cz();
   }
   c32 hy0 = cz();
   float trg = 0.f;   // tr(G_c) (mixed modes)
-  // U = 16 and 32, FP32, iterations in the same launch: the inverse keeps its lazy
+  // U = 16, FP32, iterations in the same launch: the inverse keeps its lazy
   // scales (B^{-1} = 2 D - D S D, D = diag(pv): off the diagonal
   // -S_uv pv_u pv_v), which every product applies to its operand and result
   // instead of to the U x U entries.
-  constexpr bool LAZY = ((G == 32 || G == 16) && HALF == 0 && STAGE == 0);
+  constexpr bool LAZY = (G == 16 && HALF == 0 && STAGE == 0);
   float pvl = 1.f;
   auto bmat = [&](c32 q) -> c32 {
     if constexpr (LAZY) {
@@ -1717,6 +1961,8 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
       const c32 r = group_matvec<G>(A, cscale(q, pvl), u, line, gbase);
       const float tp = 2.f * pvl;
       return c32{fmaf(tp, q.re, -pvl * r.re), fmaf(tp, q.im, -pvl * r.im)};
+    } else if constexpr (BLOCKS) {
+      return block_matvec_u32(A, q, (lane & 16) == 0);
     } else {
       return group_matvec<G>(A, q, u, line, gbase);
     }
@@ -1790,9 +2036,11 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
         A[v] = up ? e : c32{e.re, -e.im};
       }
     }
+  } else if constexpr (BLOCKS) {
+    hy0 = gram_blocks_u32(a, A, lane, wave, reinterpret_cast<float*>(sm.stage + wave * kStageWave));
   } else if constexpr (G == 32 && HALF == 0) {
-    hy0 = gram_mfma_u32<true, LAZY, FACTOR, STAGE == 4>(a, A, lane, wave, reinterpret_cast<float*>(line),
-                                    reinterpret_cast<float*>(sm.stage + wave * kStageWave), &pvl);
+    hy0 = gram_mfma_u32<true, STAGE == 4>(a, A, lane, wave, reinterpret_cast<float*>(line),
+                                          reinterpret_cast<float*>(sm.stage + wave * kStageWave));
   } else if constexpr (G == 32 && HALF == 1) {
     hy0 = gram_inv_mixed_u32<_Float16, INV>(a, A, lane, wave, reinterpret_cast<c64*>(sm.stage + wave * kStageWave),
                                             trg);
