@@ -1108,7 +1108,7 @@ __device__ __forceinline__ Tile16 tile_mul(const Tile16& X, const Tile16& Y, Til
 // Inverses of the Hermitian positive definite 16 x 16 matrices T[0], T[1] (one of
 // each problem of the wave): the sweep of gj_invert_mfma_u16 with the four blocks
 // of v_mfma_f32_16x16x1f32 holding (Re T[0], Im T[0], Re T[1], Im T[1]).  Row k
-// reaches the lane groups through wave-private LDS (lds: 256 floats).
+// reaches the lane groups through wave-private LDS (lds: 288 floats).
 __device__ __forceinline__ void tile_invert_pair(Tile16 (&T)[2], int lane, float* lds) {
   const int q = lane >> 4, col = lane & 15;
   const bool odd = q & 1;   // this lane group is an imaginary block
@@ -1120,10 +1120,10 @@ __device__ __forceinline__ void tile_invert_pair(Tile16 (&T)[2], int lane, float
     s[8 + r] = T[1].re[r];
     s[12 + r] = T[1].im[r];
   }
-  float pvm = 0.f;
   float* wq = lds + 64 * q + col;                      // write: [lane group][block][column]
   const float* rq = lds + 16 * (q & 2) + col;          // read: real block of this lane group's problem
   const float* dq = lds + 16 * (q & 2);
+  float* pvs = lds + 256 + 8 * (q & 2);                // this problem's pivot reciprocals
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     const int g = k >> 2, rr = k & 3;
@@ -1139,16 +1139,14 @@ __device__ __forceinline__ void tile_invert_pair(Tile16 (&T)[2], int lane, float
     // Re: -pv (wr_i wr_j + wi_i wi_j), Im: -pv (wr_i wi_j - wi_i wr_j)
     s = __builtin_amdgcn_mfma_f32_16x16x1f32(ar, odd ? wi : wr, s, 0, 0, 0);
     s = __builtin_amdgcn_mfma_f32_16x16x1f32(ai, odd ? -wr : wi, s, 0, 0, 0);
-    pvm = isk ? pv : pvm;
-    asm volatile("" : "+v"(pvm));   // (otherwise every pivot's pv stays live until the end)
+    if (col == 0) pvs[k] = pv;   // (no vector instruction per pivot)
   }
   // T^{-1} = 2 D - D S D, D = diag(pv)
-  if (!odd) lds[16 * (q >> 1) + col] = pvm;
   wave_lds_sync();
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
-    const float pc = lds[16 * p + col];
-    const float4 v = *reinterpret_cast<const float4*>(lds + 16 * p + 4 * q);
+    const float pc = lds[256 + 16 * p + col];
+    const float4 v = *reinterpret_cast<const float4*>(lds + 256 + 16 * p + 4 * q);
     const float pr[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -1236,18 +1234,18 @@ __device__ __forceinline__ c32 gram_blocks_u32(const UlArgs& a, c32 (&A)[32], in
       cmacc(hyp[p][1], x1, d.y[p]);
     }
   };
-  // three buffers in turn: the loads of the next eight rows are in flight
-  Rows d0, d1, d2;
+  // two buffers in turn: the loads of the next eight rows are in flight
+  Rows d0, d1;
   fetch(0, d0);
   fetch(4, d1);
-  for (int s0 = 0; s0 < a.S; s0 += 12) {
-    fetch(s0 + 8, d2);    // zeros past S
+  int s0 = 0;
+  for (; s0 + 4 < a.S; s0 += 8) {
     accumulate(d0);
-    fetch(s0 + 12, d0);
+    fetch(s0 + 8, d0);    // zeros past S
     accumulate(d1);
-    fetch(s0 + 16, d1);
-    accumulate(d2);
+    fetch(s0 + 12, d1);
   }
+  if (s0 < a.S) accumulate(d0);
   // Re G_IJ = (P^T P)_IJ - M_IJ - (M_JI)^T, Im G_IJ = M_IJ - (M_JI)^T: the
   // transposes of M_00, M_10 and M_11 through the stage buffer (row pitch 17)
   Tile16 P[2], Q[2], R[2];
