@@ -84,6 +84,18 @@ __device__ __forceinline__ float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 
+// Lane K of every row of 16 lanes, on all its lanes.
+template <int K>
+__device__ __forceinline__ float bcast16(float v) { return dpp<0x150 + K>(v); }
+
+// Calls f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>).
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
+
 template <int G>
 __device__ __forceinline__ float group_sum(float v) {
   if constexpr (G >= 2) v += dpp<0xB1>(v);

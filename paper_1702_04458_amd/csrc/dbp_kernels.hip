@@ -1108,7 +1108,10 @@ __device__ __forceinline__ Tile16 tile_mul(const Tile16& X, const Tile16& Y, Til
 // Inverses of the Hermitian positive definite 16 x 16 matrices T[0], T[1] (one of
 // each problem of the wave): the sweep of gj_invert_mfma_u16 with the four blocks
 // of v_mfma_f32_16x16x1f32 holding (Re T[0], Im T[0], Re T[1], Im T[1]).  Row k
-// reaches the lane groups through wave-private LDS (lds: 288 floats).
+// reaches the lane groups through wave-private LDS (lds: 96 floats), or with
+// LANES through lane swaps (ten vector instructions more per pivot, half the
+// latency).
+template <bool LANES = false>
 __device__ __forceinline__ void tile_invert_pair(Tile16 (&T)[2], int lane, float* lds) {
   const int q = lane >> 4, col = lane & 15;
   const bool odd = q & 1;   // this lane group is an imaginary block
@@ -1120,18 +1123,35 @@ __device__ __forceinline__ void tile_invert_pair(Tile16 (&T)[2], int lane, float
     s[8 + r] = T[1].re[r];
     s[12 + r] = T[1].im[r];
   }
-  float* wq = lds + 64 * q + col;                      // write: [lane group][block][column]
+  float* wq = lds + col;                               // write: [block][column]
   const float* rq = lds + 16 * (q & 2) + col;          // read: real block of this lane group's problem
   const float* dq = lds + 16 * (q & 2);
-  float* pvs = lds + 256 + 8 * (q & 2);                // this problem's pivot reciprocals
+  float* pvs = lds + 64 + 8 * (q & 2);                 // this problem's pivot reciprocals
+  static_for<16>([&](auto kc) {
+    constexpr int k = decltype(kc)::value, g = k >> 2, rr = k & 3;
+    float w_re, w_im, d;
+    if constexpr (LANES) {
+      // problem 0's row on the lower and problem 1's on the upper wave half,
+      // then from the even or odd row of 16 lanes to both
+      auto spread = [&](float x, float y) {
+        const f32pair h = swap_halves(x, y);
+        const unsigned v = __float_as_uint(g < 2 ? h.lo : h.hi);
+        return __uint_as_float(__builtin_amdgcn_permlane16_swap(v, v, false, false)[g & 1]);
+      };
+      w_re = spread(s[rr], s[8 + rr]);
+      w_im = spread(s[4 + rr], s[12 + rr]);
+      d = bcast16<k>(w_re);
+    } else {
+      if (q == g) {   // the lane group that holds row k
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int g = k >> 2, rr = k & 3;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) wq[16 * b] = s[4 * b + rr];
-    wave_lds_sync();
-    const float w_re = rq[64 * g], w_im = rq[64 * g + 16], d = dq[64 * g + k];
-    wave_lds_sync();
+        for (int b = 0; b < 4; ++b) wq[16 * b] = s[4 * b + rr];
+      }
+      wave_lds_sync();
+      w_re = rq[0];
+      w_im = rq[16];
+      d = dq[k];
+      wave_lds_sync();
+    }
     const float pv = __builtin_amdgcn_rcpf(d);
     const bool isk = (col == k);
     const float wr = isk ? 0.f : w_re, wi = isk ? 0.f : w_im;
@@ -1140,13 +1160,13 @@ __device__ __forceinline__ void tile_invert_pair(Tile16 (&T)[2], int lane, float
     s = __builtin_amdgcn_mfma_f32_16x16x1f32(ar, odd ? wi : wr, s, 0, 0, 0);
     s = __builtin_amdgcn_mfma_f32_16x16x1f32(ai, odd ? -wr : wi, s, 0, 0, 0);
     if (col == 0) pvs[k] = pv;   // (no vector instruction per pivot)
-  }
+  });
   // T^{-1} = 2 D - D S D, D = diag(pv)
   wave_lds_sync();
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
-    const float pc = lds[256 + 16 * p + col];
-    const float4 v = *reinterpret_cast<const float4*>(lds + 256 + 16 * p + 4 * q);
+    const float pc = lds[64 + 16 * p + col];
+    const float4 v = *reinterpret_cast<const float4*>(lds + 64 + 16 * p + 4 * q);
     const float pr[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -1340,11 +1360,9 @@ __device__ __forceinline__ c32 block_matvec_u32(const c32 (&A)[32], c32 q, bool 
 // its P = Hr + Hi) as both operands; only P P^T and M = Hr Hi^T are
 // accumulated (two MFMAs per four users instead of four).  The operands come
 // from the register copy hcol (lane u of group g: Hu[i][u]) through LDS, so H
-// is read from memory once.  The 16x16 result (lane l: column l%16, rows 4(l/16)+r) goes
-// through the wave's stage buffer.
-// The result is in the split-row layout of gj_invert_sym_split16 (lane r of DPP
-// row h of the group gets entries 8h .. 8h+7 of row r).
-__device__ __forceinline__ void gram_dl_mfma_s16_u32(const c32 (&hcol)[16], c32 (&A)[8], int lane, int g, int u,
+// is read from memory once.  Leaves T in the accumulator layout (lane l: column
+// l % 16, rows 4 (l / 16) + r); M^T comes through the wave's stage buffer.
+__device__ __forceinline__ void gram_dl_mfma_s16_u32(const c32 (&hcol)[16], Tile16 (&T)[2], int lane, int g, int u,
                                                      c32* stage) {
   const int q = lane >> 4, r16 = lane & 15;
   f32x4 re[2], im[2];
@@ -1371,23 +1389,59 @@ __device__ __forceinline__ void gram_dl_mfma_s16_u32(const c32 (&hcol)[16], c32 
       im[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j].re, x[j].im, im[p], 0, 0, 0);   // M = Hr Hi^T
     }
   }
+  // Re G[i][j] = (P P^T)[i][j] - M[i][j] - M[j][i], Im G[i][j] = M[i][j] - M[j][i]
+  float* st = reinterpret_cast<float*>(stage);
 #pragma unroll
   for (int p = 0; p < 2; ++p)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) stage[p * 256 + (4 * q + r) * 16 + r16] = c32{re[p][r], im[p][r]};
+    for (int r = 0; r < 4; ++r) st[(16 * p + 4 * q + r) * 17 + r16] = im[p][r];
   wave_lds_sync();
-  // Re A[b][v] = (P P^T)[b][v] - M[b][v] - M[v][b], Im A[b][v] = M[b][v] - M[v][b]
-  const int p = lane >> 5, b = lane & 31;
-  const float* stf = reinterpret_cast<const float*>(stage + p * 256);
-  const int r = b & 15, v0 = 8 * (b >> 4);
-  c32 row[8];
-  lds_read_vec<8>(stage + p * 256 + r * 16 + v0, row);
 #pragma unroll
-  for (int v = 0; v < 8; ++v) {
-    const float mt = stf[2 * ((v0 + v) * 16 + r) + 1];
-    A[v] = c32{row[v].re - row[v].im - mt, row[v].im - mt};
-  }
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float mt = st[(16 * p + r16) * 17 + 4 * q + r];
+      T[p].re[r] = re[p][r] - im[p][r] - mt;
+      T[p].im[r] = im[p][r] - mt;
+    }
   wave_lds_sync();
+}
+
+// Two problems' Hermitian tiles -> the split-row layout of matvec_split16: lane r
+// of row h of 16 lanes of the problem's group gets entries 8 h .. 8 h + 7 of row r
+// (column r conjugated; lane groups 2 h and 2 h + 1 hold its quarters).
+__device__ __forceinline__ void tiles_to_split_rows(const Tile16 (&T)[2], c32 (&A)[8]) {
+  auto pick = [](float x, float y, float& o0, float& o1) {
+    const f32pair ab = swap_halves(x, y);
+    const auto o = __builtin_amdgcn_permlane16_swap(__float_as_uint(ab.lo), __float_as_uint(ab.hi), false, false);
+    o0 = __uint_as_float(o[0]);
+    o1 = __uint_as_float(o[1]);
+  };
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    pick(T[0].re[r], T[1].re[r], A[r].re, A[4 + r].re);
+    pick(-T[0].im[r], -T[1].im[r], A[r].im, A[4 + r].im);
+  }
+}
+
+// The inverses of gram_dl_mfma_s16_u32 shifted by tau (identity past S), in
+// split rows.  MFMA: the sweep on the matrix cores (tile_invert_pair), shorter
+// where two waves share a SIMD (the budgeted form, 240 -> 214 us at B=256 U=32
+// C=16, 1200 subcarriers); with four waves per SIMD the vector sweep on the split
+// rows measured faster (1.31 against 1.36-1.38 ms per 38,400 subcarriers).
+template <bool MFMA>
+__device__ __forceinline__ void shift_invert_s16(Tile16 (&T)[2], float tau0, float tau1, int S, c32 (&A)[8], int lane,
+                                                 c32* line) {
+  const int q = lane >> 4, col = lane & 15;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const bool dg = 4 * q + r == col;
+    T[0].re[r] += dg ? (col < S ? tau0 : 1.f) : 0.f;
+    T[1].re[r] += dg ? (col < S ? tau1 : 1.f) : 0.f;
+  }
+  if constexpr (MFMA) tile_invert_pair<true>(T, lane, reinterpret_cast<float*>(line));
+  tiles_to_split_rows(T, A);
+  if constexpr (!MFMA) gj_invert_sym_split16(A, col, q & 1, line + (lane & 32));
 }
 
 // ---------------------------------------------------------------------------
@@ -2370,64 +2424,58 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
 #pragma unroll
     for (int i = 0; i < RS; ++i) hrow[i] = (active && ra < S) ? Hk[(size_t)ra * sa + (size_t)(r0 + i) * su] : cz();
   }
-  // The Gram H_c^H H_c, (H_c^H H_c)[a][b] = sum_u conj(Hu[a][u]) Hu[b][u], into
-  // M (rows a < S; M must hold zeros).  Every lane of the wave takes part.
+  // (H_c^H H_c)[a][b] = sum_u conj(Hu[a][u]) Hu[b][u] into M (rows a < S; M must
+  // hold zeros), where it is not formed on the matrix cores.  Every lane of
+  // the wave takes part.
   auto gram_into = [&](c32 (&M)[NR]) {
-    if constexpr (ASPLIT) {
-      gram_dl_mfma_s16_u32(hcol, M, lane, g, u, sm.stage + wave * kStageWave);
-    } else {
-      // Row b of Hu_c is broadcast from the stage buffer of this wave.
-      c32* stage = sm.stage + wave * kStageWave;
-      for (int b = 0; b < S; ++b) {
-        // lane u of the group publishes Hu[b][u] = hcol[b]
-        c32 hb = cz();
+    // Row b of Hu_c is broadcast from the stage buffer of this wave.
+    c32* stage = sm.stage + wave * kStageWave;
+    for (int b = 0; b < S; ++b) {
+      // lane u of the group publishes Hu[b][u] = hcol[b]
+      c32 hb = cz();
 #pragma unroll
-        for (int i = 0; i < SG; ++i)
-          if (i == b) hb = hcol[i];
-        stage[lane] = hb;
-        wave_lds_sync();
-        c32 acc = cz();
+      for (int i = 0; i < SG; ++i)
+        if (i == b) hb = hcol[i];
+      stage[lane] = hb;
+      wave_lds_sync();
+      c32 acc = cz();
 #pragma unroll
-        for (int v0 = 0; v0 < RS; v0 += 8) {
-          c32 row[8];
-          lds_read_vec<8>(stage + gbase + r0 + v0, row);
+      for (int v0 = 0; v0 < RS; v0 += 8) {
+        c32 row[8];
+        lds_read_vec<8>(stage + gbase + r0 + v0, row);
 #pragma unroll
-          for (int v = 0; v < 8; ++v) cmacc(acc, hrow[v0 + v], row[v]);
-        }
-        wave_lds_sync();
-        if (SPLIT) acc = c32{pair_sum<SG>(acc.re), pair_sum<SG>(acc.im)};
-#pragma unroll
-        for (int i = 0; i < SG; ++i)
-          if (i == b) M[i] = (u < S) ? acc : cz();
+        for (int v = 0; v < 8; ++v) cmacc(acc, hrow[v0 + v], row[v]);
       }
+      wave_lds_sync();
+      if (SPLIT) acc = c32{pair_sum<SG>(acc.re), pair_sum<SG>(acc.im)};
+#pragma unroll
+      for (int i = 0; i < SG; ++i)
+        if (i == b) M[i] = (u < S) ? acc : cz();
     }
   };
-  // A_c = H_c^H H_c + rho^{-1} I_S
+  // A_c = H_c^H H_c + rho^{-1} I_S (identity past S) and its inverse
   const float irho = 1.0f / a.rho;
-  // M holds H_c^H H_c; leaves (H_c^H H_c + tau I)^{-1} (identity past S)
   auto shift_invert = [&](c32 (&M)[NR], float tau) {
-    if constexpr (ASPLIT) {
-      const int h = u >> 4, r = u & 15;
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (8 * h + i == r) M[i].re += (r < S) ? tau : 1.0f;
-      gj_invert_sym_split16(M, r, h, line + gbase);
-    } else {
-#pragma unroll
-      for (int v = 0; v < SG; ++v)
-        if (v == u) M[v].re += (u < S) ? tau : 1.0f;
-      gj_invert<SG>(M, u, line, gbase);
-    }
+    for (int v = 0; v < NR; ++v)
+      if (v == u) M[v].re += (u < S) ? tau : 1.0f;
+    gj_invert<NR>(M, u, line, gbase);
   };
-  gram_into(A);
   // the budgeted step inverts the Gram again at other shifts
   constexpr bool KEEP = BUDGET && ASPLIT;
-  c32 gk[KEEP ? 8 : 1];
-  if constexpr (KEEP) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) gk[i] = A[i];
+  Tile16 gk[KEEP ? 2 : 1];
+  if constexpr (ASPLIT) {
+    Tile16 T[2];
+    gram_dl_mfma_s16_u32(hcol, T, lane, g, u, sm.stage + wave * kStageWave);
+    if constexpr (KEEP) {
+      gk[0] = T[0];
+      gk[KEEP ? 1 : 0] = T[1];
+    }
+    shift_invert_s16<BUDGET>(T, irho, irho, S, A, lane, line);
+  } else {
+    gram_into(A);
+    shift_invert(A, irho);
   }
-  shift_invert(A, irho);
   if constexpr (LATE_H) {
     // Transpose the S x G tile of each problem through the wave's stage
     // buffer, one problem at a time: entry (i, w) at i (G + 2) + w.  The
@@ -2462,10 +2510,11 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
     for (int i = 0; i < NR; ++i) Mt[i] = A[i];
   }
   if constexpr (KEEP) {
-    // the Gram's rows wait in the wave's stage buffer, which is free from here
-    // on with the split rows (lane-private slots)
+    // the Gram waits in the wave's stage buffer, which is free from here on
+    // with the split rows (lane-private slots)
+    float* st = reinterpret_cast<float*>(sm.stage + wave * kStageWave) + lane;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) sm.stage[wave * kStageWave + i * 64 + lane] = gk[i];
+    for (int i = 0; i < 16; ++i) st[64 * i] = (i & 4) ? gk[KEEP ? i >> 3 : 0].im[i & 3] : gk[KEEP ? i >> 3 : 0].re[i & 3];
   }
 
   // Broadcast line of the iterations, in the wave's stage buffer (free once
@@ -2586,14 +2635,21 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
           // (a problem that is done or below its budget inverts at its old shift again)
           if (need) tauM += d;
           if constexpr (KEEP) {
+            const float* st = reinterpret_cast<const float*>(sm.stage + wave * kStageWave) + lane;
+            Tile16 T[2];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) Mt[i] = sm.stage[wave * kStageWave + i * 64 + lane];
+            for (int i = 0; i < 16; ++i) {
+              if (i & 4) T[i >> 3].im[i & 3] = st[64 * i];
+              else T[i >> 3].re[i & 3] = st[64 * i];
+            }
+            auto tau_of = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tauM), l)); };
+            shift_invert_s16<true>(T, tau_of(0), tau_of(32), S, Mt, lane, line);
           } else {
 #pragma unroll
             for (int i = 0; i < NR; ++i) Mt[i] = cz();
             gram_into(Mt);
+            shift_invert(Mt, tauM);
           }
-          shift_invert(Mt, tauM);
         }
       }
       return xa;
