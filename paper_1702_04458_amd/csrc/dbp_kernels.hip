@@ -1080,41 +1080,35 @@ __device__ __forceinline__ c32 gram_mfma_u16(const UlArgs& a, c32 (&A)[16], int 
 // matrix instructions do not run beside the vector units, so their time adds
 // to the vector time, and the full 32 x 32 sweep was two thirds of the
 // kernel: 128 of its 192 v_mfma_f32_32x32x2f32 (72 cycles each).  The blocks
-// take 64 v_mfma_f32_16x16x1f32 (both problems' 16-pivot sweeps at once) and
-// 96 v_mfma_f32_16x16x4f32 (33 cycles each) instead, and the Gram skips the
-// block below the diagonal.
-// Every product is of the form X^H Y, for which a lane's accumulator registers
-// are its operands: lane 16 q + c holds X[4 q + r][c] and Y[4 q + r][c], and step
-// r of the product takes rows 4 q + r, q = 0 .. 3, as its four K slots.
+// take 128 v_mfma_f32_16x16x1f32 (both problems at once; the first 16 pivots
+// sweep P, Q and R, the others R alone) and 32 v_mfma_f32_16x16x4f32 (33 cycles
+// each) instead, and the Gram skips the block below the diagonal.
+// W and R - Q^H W come out of the sweep of P's pivots, not from products with
+// the explicit Pi: those would lose a factor of P's condition number (on
+// antenna-correlated channels, coefficient 0.9, ten times the sweep's error).
+// The product X^H = Si W^H is of the form A^H B, for which a lane's accumulator
+// registers are its operands: lane 16 q + c holds A[4 q + r][c] and
+// B[4 q + r][c], and step r of the product takes rows 4 q + r, q = 0 .. 3, as
+// its four K slots.
 // ---------------------------------------------------------------------------
 struct Tile16 {
   f32x4 re, im;
 };
 
-// C + sgn X^H Y (SUB: sgn = -1)
-template <bool SUB>
-__device__ __forceinline__ Tile16 tile_mul(const Tile16& X, const Tile16& Y, Tile16 C) {
+// X^H Y
+__device__ __forceinline__ Tile16 tile_mul(const Tile16& X, const Tile16& Y) {
+  Tile16 C{};
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const float xr = SUB ? -X.re[r] : X.re[r], xi = SUB ? -X.im[r] : X.im[r];
-    C.re = __builtin_amdgcn_mfma_f32_16x16x4f32(xr, Y.re[r], C.re, 0, 0, 0);
-    C.im = __builtin_amdgcn_mfma_f32_16x16x4f32(xr, Y.im[r], C.im, 0, 0, 0);
-    C.re = __builtin_amdgcn_mfma_f32_16x16x4f32(xi, Y.im[r], C.re, 0, 0, 0);
-    C.im = __builtin_amdgcn_mfma_f32_16x16x4f32(-xi, Y.re[r], C.im, 0, 0, 0);
+    C.re = __builtin_amdgcn_mfma_f32_16x16x4f32(X.re[r], Y.re[r], C.re, 0, 0, 0);
+    C.im = __builtin_amdgcn_mfma_f32_16x16x4f32(X.re[r], Y.im[r], C.im, 0, 0, 0);
+    C.re = __builtin_amdgcn_mfma_f32_16x16x4f32(X.im[r], Y.im[r], C.re, 0, 0, 0);
+    C.im = __builtin_amdgcn_mfma_f32_16x16x4f32(-X.im[r], Y.re[r], C.im, 0, 0, 0);
   }
   return C;
 }
 
-// Inverses of the Hermitian positive definite 16 x 16 matrices T[0], T[1] (one of
-// each problem of the wave): the sweep of gj_invert_mfma_u16 with the four blocks
-// of v_mfma_f32_16x16x1f32 holding (Re T[0], Im T[0], Re T[1], Im T[1]).  Row k
-// reaches the lane groups through wave-private LDS (lds: 96 floats), or with
-// LANES through lane swaps (ten vector instructions more per pivot, half the
-// latency).
-template <bool LANES = false>
-__device__ __forceinline__ void tile_invert_pair(Tile16 (&T)[2], int lane, float* lds) {
-  const int q = lane >> 4, col = lane & 15;
-  const bool odd = q & 1;   // this lane group is an imaginary block
+__device__ __forceinline__ f32x16 pack_tiles(const Tile16 (&T)[2]) {
   f32x16 s;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -1123,13 +1117,35 @@ __device__ __forceinline__ void tile_invert_pair(Tile16 (&T)[2], int lane, float
     s[8 + r] = T[1].re[r];
     s[12 + r] = T[1].im[r];
   }
-  float* wq = lds + col;                               // write: [block][column]
+  return s;
+}
+
+// Inverses of the Hermitian positive definite 16 x 16 matrices P[0], P[1] (one of
+// each problem of the wave): the sweep of gj_invert_mfma_u16 with the four blocks
+// of v_mfma_f32_16x16x1f32 holding (Re P[0], Im P[0], Re P[1], Im P[1]).  Row k
+// reaches the lane groups through wave-private LDS (lds: 160 floats), or with
+// LANES through lane swaps (ten vector instructions more per pivot, half the
+// latency; lds: 32 floats).
+// BORDER: the pivots also sweep the blocks of [P Q; Q^H R]: Q leaves as P^{-1} Q
+// and R as R - Q^H P^{-1} Q.
+template <bool LANES, bool BORDER>
+__device__ __forceinline__ void tile_sweep_pair(Tile16 (&P)[2], Tile16 (*Q)[2], Tile16 (*R)[2], int lane, float* lds) {
+  static_assert(!(LANES && BORDER), "the border's rows go through LDS");
+  const int q = lane >> 4, col = lane & 15;
+  const bool odd = q & 1;   // this lane group is an imaginary block
+  f32x16 s = pack_tiles(P), sq{}, sr{};
+  if constexpr (BORDER) {
+    sq = pack_tiles(*Q);
+    sr = pack_tiles(*R);
+  }
+  float* wq = lds + col;                               // write: [block][column], P then Q
   const float* rq = lds + 16 * (q & 2) + col;          // read: real block of this lane group's problem
   const float* dq = lds + 16 * (q & 2);
-  float* pvs = lds + 64 + 8 * (q & 2);                 // this problem's pivot reciprocals
+  constexpr int kPv = LANES ? 0 : 128;
+  float* pvs = lds + kPv + 8 * (q & 2);                // this problem's pivot reciprocals
   static_for<16>([&](auto kc) {
     constexpr int k = decltype(kc)::value, g = k >> 2, rr = k & 3;
-    float w_re, w_im, d;
+    float w_re, w_im, q_re = 0.f, q_im = 0.f, d;
     if constexpr (LANES) {
       // problem 0's row on the lower and problem 1's on the upper wave half,
       // then from the even or odd row of 16 lanes to both
@@ -1144,12 +1160,19 @@ __device__ __forceinline__ void tile_invert_pair(Tile16 (&T)[2], int lane, float
     } else {
       if (q == g) {   // the lane group that holds row k
 #pragma unroll
-        for (int b = 0; b < 4; ++b) wq[16 * b] = s[4 * b + rr];
+        for (int b = 0; b < 4; ++b) {
+          wq[16 * b] = s[4 * b + rr];
+          if constexpr (BORDER) wq[64 + 16 * b] = sq[4 * b + rr];
+        }
       }
       wave_lds_sync();
       w_re = rq[0];
       w_im = rq[16];
       d = dq[k];
+      if constexpr (BORDER) {
+        q_re = rq[64];
+        q_im = rq[80];
+      }
       wave_lds_sync();
     }
     const float pv = __builtin_amdgcn_rcpf(d);
@@ -1158,21 +1181,36 @@ __device__ __forceinline__ void tile_invert_pair(Tile16 (&T)[2], int lane, float
     const float ar = -pv * wr, ai = -pv * wi;
     // Re: -pv (wr_i wr_j + wi_i wi_j), Im: -pv (wr_i wi_j - wi_i wr_j)
     s = __builtin_amdgcn_mfma_f32_16x16x1f32(ar, odd ? wi : wr, s, 0, 0, 0);
-    s = __builtin_amdgcn_mfma_f32_16x16x1f32(ai, odd ? -wr : wi, s, 0, 0, 0);
+    if constexpr (BORDER) {
+      const float q1 = odd ? q_im : q_re, q2 = odd ? -q_re : q_im;
+      sq = __builtin_amdgcn_mfma_f32_16x16x1f32(ar, q1, sq, 0, 0, 0);
+      sr = __builtin_amdgcn_mfma_f32_16x16x1f32(-pv * q_re, q1, sr, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_16x16x1f32(ai, odd ? -wr : wi, s, 0, 0, 0);
+      sq = __builtin_amdgcn_mfma_f32_16x16x1f32(ai, q2, sq, 0, 0, 0);
+      sr = __builtin_amdgcn_mfma_f32_16x16x1f32(-pv * q_im, q2, sr, 0, 0, 0);
+    } else {
+      s = __builtin_amdgcn_mfma_f32_16x16x1f32(ai, odd ? -wr : wi, s, 0, 0, 0);
+    }
     if (col == 0) pvs[k] = pv;   // (no vector instruction per pivot)
   });
-  // T^{-1} = 2 D - D S D, D = diag(pv)
+  // P^{-1} = 2 D - D S D and P^{-1} Q = D S_Q, D = diag(pv)
   wave_lds_sync();
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
-    const float pc = lds[64 + 16 * p + col];
-    const float4 v = *reinterpret_cast<const float4*>(lds + 64 + 16 * p + 4 * q);
+    const float pc = lds[kPv + 16 * p + col];
+    const float4 v = *reinterpret_cast<const float4*>(lds + kPv + 16 * p + 4 * q);
     const float pr[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float sc = -pc * pr[r], dg = (4 * q + r == col) ? 2.f * pc : 0.f;
-      T[p].re[r] = fmaf(sc, s[8 * p + r], dg);
-      T[p].im[r] = sc * s[8 * p + 4 + r];
+      P[p].re[r] = fmaf(sc, s[8 * p + r], dg);
+      P[p].im[r] = sc * s[8 * p + 4 + r];
+      if constexpr (BORDER) {
+        (*Q)[p].re[r] = pr[r] * sq[8 * p + r];
+        (*Q)[p].im[r] = pr[r] * sq[8 * p + 4 + r];
+        (*R)[p].re[r] = sr[8 * p + r];
+        (*R)[p].im[r] = sr[8 * p + 4 + r];
+      }
     }
   }
   wave_lds_sync();
@@ -1293,13 +1331,8 @@ __device__ __forceinline__ c32 gram_blocks_u32(const UlArgs& a, c32 (&A)[32], in
       R[p].im[r] = mm[p][3][r] - mt[2][r];
     }
   }
-  tile_invert_pair(P, lane, stage);   // Pi (Hermitian: Pi^H Q = Pi Q)
-  Tile16 W[2], V[2];
-#pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    W[p] = tile_mul<false>(P[p], Q[p], Tile16{});
-    R[p] = tile_mul<true>(Q[p], W[p], R[p]);
-  }
+  tile_sweep_pair<false, true>(P, &Q, &R, lane, stage);   // Pi, W and R - Q^H W
+  Tile16 (&W)[2] = Q, V[2];
   // V = W^H, for X^H = Si W^H
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
@@ -1316,10 +1349,10 @@ __device__ __forceinline__ c32 gram_blocks_u32(const UlArgs& a, c32 (&A)[32], in
     }
     wave_lds_sync();
   }
-  tile_invert_pair(R, lane, stage);   // Si
+  tile_sweep_pair<false, false>(R, nullptr, nullptr, lane, stage);   // Si
   Tile16 X[2];
 #pragma unroll
-  for (int p = 0; p < 2; ++p) X[p] = tile_mul<false>(R[p], V[p], Tile16{});
+  for (int p = 0; p < 2; ++p) X[p] = tile_mul(R[p], V[p]);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     float l_re[4] = {P[0].re[r], W[0].re[r], P[1].re[r], W[1].re[r]};
@@ -1425,7 +1458,7 @@ __device__ __forceinline__ void tiles_to_split_rows(const Tile16 (&T)[2], c32 (&
 }
 
 // The inverses of gram_dl_mfma_s16_u32 shifted by tau (identity past S), in
-// split rows.  MFMA: the sweep on the matrix cores (tile_invert_pair), shorter
+// split rows.  MFMA: the sweep on the matrix cores (tile_sweep_pair), shorter
 // where two waves share a SIMD (the budgeted form, 240 -> 214 us at B=256 U=32
 // C=16, 1200 subcarriers); with four waves per SIMD the vector sweep on the split
 // rows measured faster (1.31 against 1.36-1.38 ms per 38,400 subcarriers).
@@ -1439,7 +1472,7 @@ __device__ __forceinline__ void shift_invert_s16(Tile16 (&T)[2], float tau0, flo
     T[0].re[r] += dg ? (col < S ? tau0 : 1.f) : 0.f;
     T[1].re[r] += dg ? (col < S ? tau1 : 1.f) : 0.f;
   }
-  if constexpr (MFMA) tile_invert_pair<true>(T, lane, reinterpret_cast<float*>(line));
+  if constexpr (MFMA) tile_sweep_pair<true, false>(T, nullptr, nullptr, lane, reinterpret_cast<float*>(line));
   tiles_to_split_rows(T, A);
   if constexpr (!MFMA) gj_invert_sym_split16(A, col, q & 1, line + (lane & 32));
 }
@@ -2471,7 +2504,8 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
       gk[0] = T[0];
       gk[KEEP ? 1 : 0] = T[1];
     }
-    shift_invert_s16<BUDGET>(T, irho, irho, S, A, lane, line);
+    // (the vector sweep in both forms: a budget that never binds changes nothing)
+    shift_invert_s16<false>(T, irho, irho, S, A, lane, line);
   } else {
     gram_into(A);
     shift_invert(A, irho);
