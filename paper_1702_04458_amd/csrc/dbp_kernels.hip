@@ -1538,14 +1538,35 @@ __device__ __forceinline__ void tile_conj_transpose(const f32x16& sre, const f32
   }
 }
 
-// The swept matrix S stays Hermitian, so tile (1, 0) is tile (0, 1)^H
-// throughout.  While the pivots of the first block column are swept (rows
-// from tiles (0, 0), (0, 1)) tile (1, 0) is not updated; it is formed as
-// (0, 1)^H before the second block's pivots (rows from tiles (1, 0), (1, 1)),
-// which in turn leave tile (0, 1) alone until it is formed as (1, 0)^H at the
-// end: six matrix-core updates per pivot instead of eight.
-__device__ __forceinline__ void gj_invert_mfma_u64(f32x16 (&re)[2][2], f32x16 (&im)[2][2], int lane, float rho,
-                                                   float* line, float* stage) {
+// X^H Y for 32 x 32 accumulator tiles (real and imaginary parts): register r of
+// both operands holds one row per lane half, the two K slots of a step.
+__device__ __forceinline__ void acc_mul(const f32x16& xr, const f32x16& xi, const f32x16& yr, const f32x16& yi,
+                                        f32x16& cr, f32x16& ci) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    cr = __builtin_amdgcn_mfma_f32_32x32x2f32(xr[r], yr[r], cr, 0, 0, 0);
+    ci = __builtin_amdgcn_mfma_f32_32x32x2f32(xr[r], yi[r], ci, 0, 0, 0);
+    cr = __builtin_amdgcn_mfma_f32_32x32x2f32(xi[r], yi[r], cr, 0, 0, 0);
+    ci = __builtin_amdgcn_mfma_f32_32x32x2f32(-xi[r], yr[r], ci, 0, 0, 0);
+  }
+}
+
+// U = 64: B = G + rho I as 32 x 32 blocks [P Q; Q^H R] (accumulator tiles (0, 0),
+// (0, 1), (1, 1); (1, 0) is not read), factored as at U = 32 (gram_blocks_u32).
+// The first 32 pivots sweep all three tiles (six 32x32x2 instructions each) and
+// leave Pi, W and R - Q^H W, the other 32 sweep the last tile alone (two); the
+// product X^H = Si W^H takes 64.  The sweep keeps lazy row and column scales
+// (see gj_invert_mfma_u32) and does not negate the diagonal.  Against the sweep
+// of the whole matrix (six per pivot throughout): 320 instead of 384, half the
+// vector instructions in the second half, products without LDS, and on
+// ill-conditioned clusters a smaller error.
+// FULL: A receives row u of B^{-1} (one more product, Pi + X W^H).  Otherwise
+// lane u < 32 receives column u of Pi in A[0 .. 31] and of X^H in A[32 .. 63],
+// lane 32 + u column u of W and of Si, for block_matvec_u64.  f2 (may be null):
+// ||B^{-1}||_F^2.
+template <bool FULL>
+__device__ __forceinline__ void invert_blocks_u64(f32x16 (&re)[2][2], f32x16 (&im)[2][2], int lane, float rho,
+                                                  float* line, float* stage, c32 (&A)[64], float* f2) {
   const int h = lane >> 5, col = lane & 31;
   // B = G + rho I
 #pragma unroll
@@ -1554,49 +1575,117 @@ __device__ __forceinline__ void gj_invert_mfma_u64(f32x16 (&re)[2][2], f32x16 (&
     re[0][0][r] += dg ? rho : 0.f;
     re[1][1][r] += dg ? rho : 0.f;
   }
-  float pvv[2] = {0.f, 0.f};
 #pragma unroll
   for (int kk = 0; kk < 64; ++kk) {
     const int Ik = kk / 32, kr = kk % 32;
     const int rr = 4 * (kr / 8) + (kr % 4);
     const int hk = (kr / 4) & 1;
-    if (kk == 32) tile_conj_transpose(re[0][1], im[0][1], re[1][0], im[1][0], h, col, stage);
     const float d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(re[Ik][Ik][rr]), kr + 32 * hk));
     const float pv = __builtin_amdgcn_rcpf(d);
-    // row kk with entry kk zeroed at the source lanes, as in gj_invert_mfma_u32
-    float first[2], second[2];
+    const bool isk = (col == kr);
+    float first[2], second[2], At[2];
 #pragma unroll
     for (int J = 0; J < 2; ++J) {
+      if (J < Ik) continue;
+      // row kk on both lane halves, entry kk zeroed at the source lanes
+      // (lanes < 32 get (Re, Im), lanes >= 32 (Im, Re), with (Im, -Re) as the
+      // imaginary update's B operand)
+      const bool z = isk && J == Ik;
       const float sr = re[Ik][J][rr], si = im[Ik][J][rr];
-      const bool isk = (32 * J + col == kk);
-      // (Im, -Re) as the imaginary update's B operand, as at U = 32
-      const float srm = isk ? 0.f : sr, sim = isk ? 0.f : si, srn = isk ? 0.f : -sr;
+      const float srm = z ? 0.f : sr, sim = z ? 0.f : si, srn = z ? 0.f : -sr;
       const auto fs = __builtin_amdgcn_permlane32_swap(__float_as_uint(srm), __float_as_uint(sim), false, false);
       const auto sf = __builtin_amdgcn_permlane32_swap(__float_as_uint(sim), __float_as_uint(srn), false, false);
       first[J] = __uint_as_float(fs[hk]);
       second[J] = __uint_as_float(sf[hk]);
-      re[Ik][J][rr] = (isk && h == hk) ? -sr : sr;
-    }
-    float Are[2], Aim[2];
-#pragma unroll
-    for (int J = 0; J < 2; ++J) {
-      Are[J] = -pv * first[J];
-      Aim[J] = Are[J];
+      At[J] = -pv * first[J];
     }
 #pragma unroll
     for (int I = 0; I < 2; ++I)
 #pragma unroll
-      for (int J = 0; J < 2; ++J) {
-        if (I != J && I != Ik) continue;   // the off-diagonal tile outside the pivot's block row
-        re[I][J] = __builtin_amdgcn_mfma_f32_32x32x2f32(Are[I], first[J], re[I][J], 0, 0, 0);
-        im[I][J] = __builtin_amdgcn_mfma_f32_32x32x2f32(Aim[I], second[J], im[I][J], 0, 0, 0);
+      for (int J = I; J < 2; ++J) {
+        if (I < Ik) continue;
+        re[I][J] = __builtin_amdgcn_mfma_f32_32x32x2f32(At[I], first[J], re[I][J], 0, 0, 0);
+        im[I][J] = __builtin_amdgcn_mfma_f32_32x32x2f32(At[I], second[J], im[I][J], 0, 0, 0);
       }
-#pragma unroll
-    for (int J = 0; J < 2; ++J) pvv[J] = (32 * J + col == kk) ? pv : pvv[J];
-    asm volatile("" : "+v"(pvv[0]), "+v"(pvv[1]));
+    if (lane == 0) line[kk] = pv;
   }
-  tile_conj_transpose(re[1][0], im[1][0], re[0][1], im[0][1], h, col, stage);
-  gj_unscale_u64(re, im, pvv, 1.f, lane, line);
+  wave_lds_sync();
+  // Pi and Si: 2 D - D S D, W: D S (rows)
+#pragma unroll
+  for (int I = 0; I < 2; ++I) {
+    const float pc = line[32 * I + col];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 v = *reinterpret_cast<const float4*>(line + 32 * I + 8 * g + 4 * h);
+      const float pr[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int r = 4 * g + t;
+        const float sc = -pc * pr[t], dg = (8 * g + 4 * h + t == col) ? 2.f * pc : 0.f;
+        re[I][I][r] = fmaf(sc, re[I][I][r], dg);
+        im[I][I][r] *= sc;
+        if (I == 0) {
+          re[0][1][r] *= pr[t];
+          im[0][1][r] *= pr[t];
+        }
+      }
+    }
+  }
+  wave_lds_sync();
+  // X^H = Si W^H into tile (1, 0)
+  f32x16 vr, vi;
+  tile_conj_transpose(re[0][1], im[0][1], vr, vi, h, col, stage);
+  re[1][0] = im[1][0] = f32x16{};
+  acc_mul(re[1][1], im[1][1], vr, vi, re[1][0], im[1][0]);
+  if constexpr (FULL) {
+    acc_mul(re[1][0], im[1][0], vr, vi, re[0][0], im[0][0]);   // Pi + X W^H
+    tile_conj_transpose(re[1][0], im[1][0], re[0][1], im[0][1], h, col, stage);   // X
+  } else if (f2) {
+    f32x16 tr = re[0][0], ti = im[0][0];
+    acc_mul(re[1][0], im[1][0], vr, vi, tr, ti);
+    float n = 0.f, off = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      n = fmaf(tr[r], tr[r], fmaf(ti[r], ti[r], n));
+      n = fmaf(re[1][1][r], re[1][1][r], fmaf(im[1][1][r], im[1][1][r], n));
+      off = fmaf(re[1][0][r], re[1][0][r], fmaf(im[1][0][r], im[1][0][r], off));
+    }
+    *f2 = group_sum<64>(fmaf(2.f, off, n));
+  }
+  // to lanes: column u of the left tile to lane u, of the right one to lane 32 + u
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m0 = 8 * (r / 4) + (r % 4);
+    const f32pair lr = swap_halves(re[0][0][r], FULL ? -re[0][1][r] : re[0][1][r]);
+    const f32pair hr = swap_halves(FULL ? -re[1][0][r] : re[1][0][r], re[1][1][r]);
+    // FULL: rows (columns conjugated)
+    const f32pair li = swap_halves(FULL ? -im[0][0][r] : im[0][0][r], im[0][1][r]);
+    const f32pair hi = swap_halves(im[1][0][r], FULL ? -im[1][1][r] : im[1][1][r]);
+    A[m0] = c32{lr.lo, li.lo};
+    A[m0 + 4] = c32{lr.hi, li.hi};
+    A[32 + m0] = c32{hr.lo, hi.lo};
+    A[32 + m0 + 4] = c32{hr.hi, hi.hi};
+  }
+}
+
+// B^{-1} q from the blocks of invert_blocks_u64 (as block_matvec_u32): the two
+// rows of 16 lanes of an operand are handed to all four by three swaps.
+__device__ __forceinline__ c32 block_matvec_u64(const c32 (&A)[64], c32 q, bool upper) {
+  auto spread = [](float v, int half, float& r0, float& r1) {
+    const unsigned u = __float_as_uint(v);
+    const auto e = __builtin_amdgcn_permlane16_swap(u, u, false, false);   // even | odd rows, in pairs
+    r0 = __uint_as_float(__builtin_amdgcn_permlane32_swap(e[0], e[0], false, false)[half]);
+    r1 = __uint_as_float(__builtin_amdgcn_permlane32_swap(e[1], e[1], false, false)[half]);
+  };
+  c32 x0, x1;
+  spread(q.re, 0, x0.re, x1.re);
+  spread(q.im, 0, x0.im, x1.im);
+  const c32 a = cadd(matvec16c<0>(A, x0), matvec16c<16>(A, x1));     // Pi q_1 | W^H q_1
+  const c32 t = csub(q, a);                                          // (upper half of the wave) q_2 - W^H q_1
+  spread(t.re, 1, x0.re, x1.re);
+  spread(t.im, 1, x0.im, x1.im);
+  const c32 b = cadd(matvec16c<32>(A, x0), matvec16c<48>(A, x1));    // X t | Si t
+  return upper ? csub(a, b) : b;
 }
 
 // accumulator tiles -> lane-row layout: lane u < 32 takes column u of tile
@@ -1625,7 +1714,8 @@ __device__ __forceinline__ c32 combine_hy_u64(c32 e0, c32 e1, int h) {
   return c32{yr.lo + yr.hi, yi.lo + yi.hi};
 }
 
-template <bool INVERT>
+// INVERT: 0 the Gram (rows of G in A), 1 its block factors, 2 rows of the inverse.
+template <int INVERT>
 __device__ __forceinline__ c32 gram_mfma_u64(const UlArgs& a, c32 (&A)[64], int lane, int wave, float* line,
                                              float* stage) {
   const int h = lane >> 5, col = lane & 31;
@@ -1663,8 +1753,7 @@ __device__ __forceinline__ c32 gram_mfma_u64(const UlArgs& a, c32 (&A)[64], int 
     for (int I = 0; I < 2; ++I)
 #pragma unroll
       for (int J = 0; J < 2; ++J) {
-        // with INVERT tile (1, 0) of G is never read before the inverse forms
-        // it as tile (0, 1)^H, so its P^T P part is not accumulated
+        // with INVERT tile (1, 0) of G is not read: its P^T P part is not accumulated
         if (!(INVERT && I == 1 && J == 0))
           re[I][J] = __builtin_amdgcn_mfma_f32_32x32x2f32(ps[I], ps[J], re[I][J], 0, 0, 0);        // P^T P
         im[I][J] = __builtin_amdgcn_mfma_f32_32x32x2f32(xs[I].re, xs[J].im, im[I][J], 0, 0, 0);   // M
@@ -1698,7 +1787,7 @@ __device__ __forceinline__ c32 gram_mfma_u64(const UlArgs& a, c32 (&A)[64], int 
   };
   {
     float t01[16] = {}, t10[16];
-    if constexpr (!INVERT) transposed(im[0][1], t01);
+    if constexpr (INVERT == 0) transposed(im[0][1], t01);
     transposed(im[1][0], t10);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -1720,8 +1809,10 @@ __device__ __forceinline__ c32 gram_mfma_u64(const UlArgs& a, c32 (&A)[64], int 
       im[D][D][r] -= td[r];
     }
   }
-  if (INVERT) gj_invert_mfma_u64(re, im, lane, a.rho, line, stage);
-  acc_to_rows_u64(re, im, A, h);
+  if constexpr (INVERT != 0)
+    invert_blocks_u64<INVERT == 2>(re, im, lane, a.rho, line, stage, A, nullptr);
+  else
+    acc_to_rows_u64(re, im, A, h);
   return combine_hy_u64(hy0, hy1, h);
 }
 
@@ -1776,9 +1867,9 @@ __device__ __forceinline__ void gj_invert_split16_u64(f32x16 (&re)[2][2], f32x16
 // each 16-row chunk at column 32I + l%32 (A) and 32J + l%32 (B).  Then the
 // Gauss-Jordan inverse on the matrix cores: FP32 (INV = 0) or split FP16 on
 // the normalised Gram (INV = 2).
-template <typename HT, int INV>
+template <typename HT, int INV, bool FACTOR>
 __device__ __forceinline__ c32 gram_inv_mixed_u64(const UlArgs& a, c32 (&A)[64], int lane, int wave,
-                                                  float* line, float* stage, float& trg) {
+                                                  float* line, float* stage, float& trg, float* f2) {
   typedef typename HalfMma<HT>::V V;
   const int h = lane >> 5, col = lane & 31;
   const int ls = wave / a.Cp, c = wave % a.Cp;
@@ -1840,6 +1931,7 @@ __device__ __forceinline__ c32 gram_inv_mixed_u64(const UlArgs& a, c32 (&A)[64],
     for (int I = 0; I < 2; ++I)
 #pragma unroll
       for (int J = 0; J < 2; ++J) {
+        if (INV == 0 && I > J) continue;   // the block inverse does not read it
         re[I][J] = HalfMma<HT>::mma(rh[I], rh[J], re[I][J]);
         re[I][J] = HalfMma<HT>::mma(rh[I], rl[J], re[I][J]);
         re[I][J] = HalfMma<HT>::mma(rl[I], rh[J], re[I][J]);
@@ -1867,8 +1959,8 @@ __device__ __forceinline__ c32 gram_inv_mixed_u64(const UlArgs& a, c32 (&A)[64],
   if (INV == 2)
     gj_invert_split16_u64(re, im, lane, ldexpf(a.rho, 2 * ex - sh), ldexpf(1.f, 2 * ex - sh), line);
   else
-    gj_invert_mfma_u64(re, im, lane, a.rho, line, stage);
-  acc_to_rows_u64(re, im, A, h);
+    invert_blocks_u64<FACTOR>(re, im, lane, a.rho, line, stage, A, a.cond_max > 0.f ? f2 : nullptr);
+  if constexpr (INV == 2) acc_to_rows_u64(re, im, A, h);
   return combine_hy_u64(hy0, hy1, h);
 }
 
@@ -2010,6 +2102,7 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
   constexpr bool RESIDENT = (STAGE == 2 || STAGE == 3);   // iterations against stored factors
   constexpr bool FACTOR = (STAGE == 1 || STAGE == 4);     // preprocessing only
   constexpr bool BLOCKS = (G == 32 && HALF == 0 && STAGE == 0);   // the inverse as 16 x 16 block factors
+  constexpr bool BLOCKS64 = (G == 64 && INV == 0 && STAGE == 0);  // the same with 32 x 32 blocks
   extern __shared__ float4 smem_raw[];
   const int nw = blockDim.x >> 6;
   Smem sm = carve(reinterpret_cast<c32*>(smem_raw), nw);
@@ -2028,12 +2121,13 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
   c32 A[G];
   // (the U = 16 Gram and the U = 32 factor staging write every entry of every
   // lane's row: no clearing)
-  if constexpr (!(G == 16 && !RESIDENT) && !(G == 32 && RESIDENT) && !BLOCKS) {
+  if constexpr (!(G == 16 && !RESIDENT) && !(G == 32 && RESIDENT) && !BLOCKS && !BLOCKS64) {
 #pragma unroll
     for (int v = 0; v < G; ++v) A[v] = cz();
   }
   c32 hy0 = cz();
   float trg = 0.f;   // tr(G_c) (mixed modes)
+  float f2b = 0.f;   // ||B_c^{-1}||_F^2 (mixed modes, block factors, FP64 factor rule)
   // U = 16, FP32, iterations in the same launch: the inverse keeps its lazy
   // scales (B^{-1} = 2 D - D S D, D = diag(pv): off the diagonal
   // -S_uv pv_u pv_v), which every product applies to its operand and result
@@ -2048,6 +2142,8 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
       return c32{fmaf(tp, q.re, -pvl * r.re), fmaf(tp, q.im, -pvl * r.im)};
     } else if constexpr (BLOCKS) {
       return block_matvec_u32(A, q, (lane & 16) == 0);
+    } else if constexpr (BLOCKS64) {
+      return block_matvec_u64(A, q, lane < 32);
     } else {
       return group_matvec<G>(A, q, u, line, gbase);
     }
@@ -2140,14 +2236,14 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
       gj_invert<G>(A, u, line, gbase);
     }
   } else if constexpr (G == 64 && HALF == 0) {
-    hy0 = gram_mfma_u64<true>(a, A, lane, wave, reinterpret_cast<float*>(line),
+    hy0 = gram_mfma_u64<FACTOR ? 2 : 1>(a, A, lane, wave, reinterpret_cast<float*>(line),
                               reinterpret_cast<float*>(sm.stage + wave * kStageWave));
   } else if constexpr (G == 64 && HALF == 1) {
-    hy0 = gram_inv_mixed_u64<_Float16, INV>(a, A, lane, wave, reinterpret_cast<float*>(line),
-                                            reinterpret_cast<float*>(sm.stage + wave * kStageWave), trg);
+    hy0 = gram_inv_mixed_u64<_Float16, INV, FACTOR>(a, A, lane, wave, reinterpret_cast<float*>(line),
+                                            reinterpret_cast<float*>(sm.stage + wave * kStageWave), trg, &f2b);
   } else if constexpr (G == 64 && HALF == 2) {
-    hy0 = gram_inv_mixed_u64<__bf16, INV>(a, A, lane, wave, reinterpret_cast<float*>(line),
-                                          reinterpret_cast<float*>(sm.stage + wave * kStageWave), trg);
+    hy0 = gram_inv_mixed_u64<__bf16, INV, FACTOR>(a, A, lane, wave, reinterpret_cast<float*>(line),
+                                          reinterpret_cast<float*>(sm.stage + wave * kStageWave), trg, &f2b);
   } else {
     hy0 = cluster_pass<G, true>(a.H, a.y, A, k, c, 0, u, g, lane, wave, active, a.B, a.S, G, a.n_sym, sm);
 #pragma unroll
@@ -2205,10 +2301,12 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
   float guard = a.guard;
   if constexpr (COND) {
     if (a.cond_max != 0.f) {
-      float f2 = 0.f;
+      float f2 = f2b;
+      if constexpr (!BLOCKS64) {
 #pragma unroll
-      for (int v = 0; v < G; ++v) f2 = fmaf(A[v].re, A[v].re, fmaf(A[v].im, A[v].im, f2));
-      f2 = group_sum<G>(f2);
+        for (int v = 0; v < G; ++v) f2 = fmaf(A[v].re, A[v].re, fmaf(A[v].im, A[v].im, f2));
+        f2 = group_sum<G>(f2);
+      }
       const float kh = (trg + (float)G * a.rho) * sqrtf(f2);
       if (u == 0) cond_slot[ls * a.Cp + c] = active ? kh : 0.f;
     }
@@ -2324,7 +2422,7 @@ __global__ void __launch_bounds__(512) dcg_ul_f32(UlArgs a) {
   else if constexpr (G == 16)
     hy0 = gram_mfma_u16(a, A, lane, wave, sm.stage + wave * kStageWave);
   else if constexpr (G == 64)
-    hy0 = gram_mfma_u64<false>(a, A, lane, wave, reinterpret_cast<float*>(line),
+    hy0 = gram_mfma_u64<0>(a, A, lane, wave, reinterpret_cast<float*>(line),
                                reinterpret_cast<float*>(sm.stage + wave * kStageWave));
   else
     hy0 = cluster_pass<G, true>(a.H, a.y, A, k, c, 0, u, g, lane, wave, active, a.B, a.S, G, a.n_sym, sm);
