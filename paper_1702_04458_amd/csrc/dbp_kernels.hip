@@ -1733,22 +1733,21 @@ __device__ __forceinline__ c32 gram_mfma_u64(const UlArgs& a, c32 (&A)[64], int 
       re[I][J] = f32x16{};
       im[I][J] = f32x16{};
     }
-  c32 x0 = cz(), x1 = cz(), yv = cz();
   // buffer loads over the problem's S rows (as in gram_mfma_u32)
   const __amdgpu_buffer_rsrc_t hrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<c32*>(Hk), 0, act ? a.S * 512 : 0, kBufferWord3);
   const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<c32*>(yk), 0, act ? a.S * 8 : 0, kBufferWord3);
-  auto fetch = [&](int s0, c32& o0, c32& o1, c32& oy) {
-    const int s = s0 + h;   // row s, columns col and 32 + col: bytes 512 s + 8 col (+ 256)
-    o0 = __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(hrs, s * 512 + col * 8, 0, 0));
-    o1 = __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(hrs, s * 512 + 256 + col * 8, 0, 0));
-    oy = __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(yrs, s * 8, 0, 0));
+  struct Rows {
+    c32 x0, x1, y;   // two rows, one per lane half
   };
-  fetch(0, x0, x1, yv);
-  for (int s0 = 0; s0 < a.S; s0 += 2) {
-    c32 n0, n1, ny;
-    if (s0 + 2 < a.S) fetch(s0 + 2, n0, n1, ny);
-    const c32 xs[2] = {x0, x1};
-    const float ps[2] = {x0.re + x0.im, x1.re + x1.im};
+  auto fetch = [&](int s0, Rows& d) {
+    const int s = s0 + h;   // row s, columns col and 32 + col: bytes 512 s + 8 col (+ 256)
+    d.x0 = __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(hrs, s * 512 + col * 8, 0, 0));
+    d.x1 = __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(hrs, s * 512 + 256 + col * 8, 0, 0));
+    d.y = __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(yrs, s * 8, 0, 0));
+  };
+  auto accumulate = [&](const Rows& d) {
+    const c32 xs[2] = {d.x0, d.x1};
+    const float ps[2] = {d.x0.re + d.x0.im, d.x1.re + d.x1.im};
 #pragma unroll
     for (int I = 0; I < 2; ++I)
 #pragma unroll
@@ -1759,12 +1758,26 @@ __device__ __forceinline__ c32 gram_mfma_u64(const UlArgs& a, c32 (&A)[64], int 
         im[I][J] = __builtin_amdgcn_mfma_f32_32x32x2f32(xs[I].re, xs[J].im, im[I][J], 0, 0, 0);   // M
       }
     // entries col and 32 + col of H_c^H y_c over the rows of this lane's parity
-    cmacc(hy0, x0, yv);
-    cmacc(hy1, x1, yv);
-    x0 = n0;
-    x1 = n1;
-    yv = ny;
+    cmacc(hy0, d.x0, d.y);
+    cmacc(hy1, d.x1, d.y);
+  };
+  // Four buffers in turn, eight rows in flight: with two waves per SIMD a step's
+  // matrix instructions (about 900 cycles for both) are shorter than a load
+  // from memory.
+  Rows d[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) fetch(2 * j, d[j]);   // zeros past S
+  int s0 = 0;
+  for (; s0 + 8 <= a.S; s0 += 8) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      accumulate(d[j]);
+      fetch(s0 + 8 + 2 * j, d[j]);
+    }
   }
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (s0 + 2 * j < a.S) accumulate(d[j]);   // uniform
   // Tile (I, J) holds P^T P and M = Hr^T Hi restricted to rows 32 I.. and
   // columns 32 J..; Re G_IJ = (P^T P)_IJ - M_IJ - (M_JI)^T and
   // Im G_IJ = M_IJ - (M_JI)^T.  The transposes go through the wave's stage
