@@ -311,7 +311,7 @@ int dbp_precode_admm(const void* H, int h_layout, const void* s, void* x, float*
 /* Uneven batches in one launch: up to DBP_MAX_BATCH frames of ADMM
  * detection (Algorithm 1, FP32) that share U but may differ in every other
  * shape and parameter (n_sc, n_sym, B, C, T, regulariser, QAM, rho, N0) run
- * in one persistent kernel over all their subcarriers, followed by one FP64
+ * in one launch over all their subcarriers, followed by one FP64
  * re-slice pass over the frames with hard decisions.  Each dbp_frame holds
  * what dbp_detect_admm takes for one frame (device pointers, caller-owned;
  * workspace as there, needed with hard decisions).  Results are

@@ -1,6 +1,7 @@
 // C ABI entry points: host-side validation, launch planning and dispatch.
 #include <hip/hip_runtime.h>
 
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -804,12 +805,10 @@ int dbp_detect_admm_batch(const dbp_frame* frames, int n_frames, int U, void* st
     total += (fr.n_sc + pl.scpb - 1) / pl.scpb;
     ++b.n;
   }
-  b.first[b.n] = total;
+  for (int i = b.n; i < dbp::kMaxBatch; ++i) b.first[i] = INT_MAX;
   if (total == 0) return ok();
   const hipStream_t hs = static_cast<hipStream_t>(stream);
-  // persistent grid: enough workgroups to fill the chip at four waves per SIMD
-  const int cap = 256 * (16 / nw > 0 ? 16 / nw : 1);
-  int st = device_status(who, dbp::launch_admm_ul_f32_batch(b, U, nw, total < cap ? total : cap, hs));
+  int st = device_status(who, dbp::launch_admm_ul_f32_batch(b, U, nw, total, hs));
   if (st || fb.n == 0) return st;
   return device_status(who, dbp::launch_admm_ul_fix64_batch(fb, U, n_slots, hs));
 }

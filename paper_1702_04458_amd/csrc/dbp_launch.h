@@ -88,7 +88,7 @@ struct DlArgs {
 constexpr int kMaxBatch = 24;
 struct UlBatch {
   UlArgs f[kMaxBatch];
-  int first[kMaxBatch + 1];   // first virtual block of each frame, first[n] = total
+  int first[kMaxBatch];   // first workgroup of each frame, INT_MAX from n on
   int n;
 };
 struct FixBatch {
@@ -99,7 +99,7 @@ struct FixBatch {
 static_assert(sizeof(UlBatch) <= 4096 && sizeof(FixBatch) <= 4096, "kernel argument blocks exceed 4 KiB");
 
 size_t smem_bytes(int nw);
-// persistent launch of grid workgroups (nw waves each) over all frames of b
+// one launch of grid workgroups (nw waves each; the sum of the frames' blocks) over all frames of b
 hipError_t launch_admm_ul_f32_batch(const UlBatch& b, int U, int nw, int grid, hipStream_t st);
 // FP64 re-slice of the flagged subcarriers of every frame of b
 hipError_t launch_admm_ul_fix64_batch(const FixBatch& b, int U, int n_slots, hipStream_t st);
