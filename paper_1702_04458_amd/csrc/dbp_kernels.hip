@@ -2069,6 +2069,275 @@ __device__ __forceinline__ c32 consensus_w(c32 wc, int buf, int ls, int u, int g
 }
 
 // ---------------------------------------------------------------------------
+// Several received vectors over one channel (U = 16, 32, 64): eight symbols at a
+// time as the 16 columns (eight real, eight imaginary parts) of 16 x 16 x 4
+// products.  A complex product M X is Re M [Xr | Xi] + Im M [-Xi | Xr], the
+// second operand a rotation of the first by eight lanes.  Rows 4 q + r of a
+// column block sit in register r of lane group q, both as an accumulator and as
+// the operand of step r, so the vectors pass from product to product without
+// moving, and the eight symbols share each barrier of the consensus.
+// Bound by the issue of the products: the vector units need 128 multiply-adds per
+// symbol, product and wave at U = 32 (512 cycles), these 64 instructions of 32
+// cycles for eight symbols (256 cycles each).  Measured, 9536 subcarriers at
+// B = 256, U = 32, C = 8, T = 5: seven symbols 783 -> 544 us, fourteen 1370 -> 852.
+// Registers: U = 32 capped at 168 (three waves per SIMD; 169 and two: 626 us for
+// seven symbols), U = 16 at 128.
+// ---------------------------------------------------------------------------
+
+// [Xr | Xi] -> [Xi | Xr], the first half times sg and the second times -sg (the
+// sign is the lane's)
+__device__ __forceinline__ float swap_parts(float x, float sg) {
+  return sg * __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xF, 0xF, true));
+}
+
+// H_c^H y_c of symbols n0 .. n0 + 7 for the problems of the wave (zero past n_sym).
+template <int G>
+__device__ __forceinline__ void syms_hy(const UlArgs& a, int n0, f32x4 (&hy)[64 / G][G / 16], int lane, int wave) {
+  constexpr int P = 64 / G, NT = G / 16;
+  const int q = lane >> 4, col = lane & 15, j = col & 7;
+  const float sg = (col & 8) ? -1.f : 1.f;   // conj(H): [yi | -yr]
+  __amdgpu_buffer_rsrc_t hrs[P], yrs[P];
+  f32x4 hi[P][NT];
+  const int nj = min(8, a.n_sym - n0);
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const int lp = wave * P + p;
+    const int ls = lp / a.Cp, c = lp % a.Cp;
+    const int k = a.blk * a.sc_per_block + ls;
+    const bool act = (k < a.n_sc) && (c < a.C);
+    const c32* Hp = act ? a.H + (size_t)k * a.B * G + (size_t)c * a.S * G : a.H;
+    const c32* yp = act ? a.y + ((size_t)k * a.n_sym + n0) * a.B + (size_t)c * a.S : a.y;
+    hrs[p] = __builtin_amdgcn_make_buffer_rsrc(const_cast<c32*>(Hp), 0, act ? a.S * G * 8 : 0, kBufferWord3);
+    yrs[p] = __builtin_amdgcn_make_buffer_rsrc(const_cast<c32*>(yp), 0, act ? ((nj - 1) * a.B + a.S) * 8 : 0, kBufferWord3);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) hy[p][t] = hi[p][t] = f32x4{};
+  }
+  struct Rows {
+    c32 h[P][NT];
+    float y[P];
+  };
+  auto fetch = [&](int s0, Rows& d) {
+    const int s = s0 + q;
+    // (an offset past the range for rows past S and symbols past n_sym: zero)
+    const unsigned yo = (s < a.S && j < nj) ? (unsigned)(j * a.B + s) * 8u + ((col & 8) ? 4u : 0u) : 0x80000000u;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        d.h[p][t] = __builtin_bit_cast(
+            c32, __builtin_amdgcn_raw_buffer_load_b64(hrs[p], s * (G * 8) + t * 128 + col * 8, 0, 0));
+      d.y[p] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(yrs[p], yo, 0, 0));
+    }
+  };
+  auto accumulate = [&](const Rows& d) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      const float ys = swap_parts(d.y[p], sg);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) hy[p][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.h[p][t].re, d.y[p], hy[p][t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) hi[p][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.h[p][t].im, ys, hi[p][t], 0, 0, 0);
+    }
+  };
+  Rows d0, d1;
+  fetch(0, d0);
+  fetch(4, d1);
+  int s0 = 0;
+  for (; s0 + 4 < a.S; s0 += 8) {
+    accumulate(d0);
+    fetch(s0 + 8, d0);
+    accumulate(d1);
+    fetch(s0 + 12, d1);
+  }
+  if (s0 < a.S) accumulate(d0);
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) hy[p][t] += hi[p][t];
+}
+
+// The rows of the lane layout (lane 16 g + i: row i of lane group g) as operands:
+// A[16 J + 4 g + s] of lane 16 q + i becomes entry (i, 16 J + 4 q + s) of group g.
+template <int G>
+__device__ __forceinline__ void rows_to_operands(c32 (&A)[G]) {
+#pragma unroll
+  for (int J = 0; J < G / 16; ++J)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      float re[4], im[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        re[m] = A[16 * J + 4 * m + s].re;
+        im[m] = A[16 * J + 4 * m + s].im;
+      }
+      transpose_groups(re);
+      transpose_groups(im);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) A[16 * J + 4 * g + s] = c32{re[g], im[g]};
+    }
+}
+
+// B^{-1} x of problem p of the wave.  BLOCK: the block factors of gram_blocks_u32
+// and invert_blocks_u64 (their conjugates), else the whole inverse.  The products
+// with the real and the imaginary parts have accumulators of their own: shorter
+// sums, and two chains in flight per row block.
+template <int G, bool BLOCK>
+__device__ __forceinline__ void syms_matvec(const c32 (&A)[G], int p, const f32x4 (&x)[G / 16], f32x4 (&out)[G / 16],
+                                            float sg) {
+  constexpr int NT = G / 16, NH = BLOCK ? NT / 2 : NT;
+  // acc[I] = sum of column blocks J0 .. J0 + NH - 1 times v[J - J0]
+  auto mul = [&](int J0, const f32x4 (&v)[NH], f32x4 (&acc)[NT]) {
+    f32x4 im[NT];
+#pragma unroll
+    for (int I = 0; I < NT; ++I) acc[I] = im[I] = f32x4{};
+#pragma unroll
+    for (int J = 0; J < NH; ++J)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float w = swap_parts(v[J][r], sg);
+#pragma unroll
+        for (int I = 0; I < NT; ++I) {
+          const c32 m = A[16 * (J0 + J) + 4 * (p * NT + I) + r];
+          acc[I] = __builtin_amdgcn_mfma_f32_16x16x4f32(m.re, v[J][r], acc[I], 0, 0, 0);
+          im[I] = __builtin_amdgcn_mfma_f32_16x16x4f32(m.im, w, im[I], 0, 0, 0);
+        }
+      }
+#pragma unroll
+    for (int I = 0; I < NT; ++I) acc[I] += im[I];
+  };
+  if constexpr (!BLOCK) {
+    mul(0, x, out);
+  } else {
+    f32x4 v[NH], b[NT];
+#pragma unroll
+    for (int J = 0; J < NH; ++J) v[J] = x[J];
+    mul(0, v, out);                                       // Pi q_1 | W^H q_1
+#pragma unroll
+    for (int J = 0; J < NH; ++J) v[J] = x[NH + J] - out[NH + J];   // t
+    mul(NH, v, b);                                        // X t | Si t
+#pragma unroll
+    for (int J = 0; J < NH; ++J) {
+      out[J] = out[J] - b[J];
+      out[NH + J] = b[NH + J];
+    }
+  }
+}
+
+// The iterations of all symbols.  A: the factors as operands; cons: the waves'
+// stage buffers.  All problems of a wave belong to one subcarrier (Cp >= 64 / G).
+// Returns the status bits of the wave's outputs.
+template <int G, bool BLOCK>
+__device__ __forceinline__ int syms_iterate(const UlArgs& a, const c32 (&A)[G], int lane, int wave, float4* cons) {
+  constexpr int P = 64 / G, NT = G / 16, pitch = kStageWave / 2;
+  constexpr bool TWO = 2 * NT * 64 <= pitch;   // two consensus buffers in turn (U = 64: one, and a second barrier)
+  const int col = lane & 15, j = col & 7, im = col >> 3;
+  const float sg = (im != 0) == BLOCK ? -1.f : 1.f;   // [-xi | xr], or with conjugated factors [xi | -xr]
+  const int wps = a.Cp / P;                           // waves of a subcarrier
+  const int w0 = wave / wps * wps;                    // the first of them
+  const int k = a.blk * a.sc_per_block + wave / wps;
+  int fl = 0, buf = 0;
+  bool act[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) act[p] = k < a.n_sc && (wave - w0) * P + p < a.C;
+  for (int n0 = 0; n0 < a.n_sym; n0 += 8) {
+    f32x4 z[P][NT], lam[P][NT], yreg[P][NT], s[NT];
+    {
+      f32x4 hy[P][NT];
+      syms_hy<G>(a, n0, hy, lane, wave);
+#pragma unroll
+      for (int p = 0; p < P; ++p) syms_matvec<G, BLOCK>(A, p, hy[p], yreg[p], sg);
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        z[p][t] = yreg[p][t];
+        lam[p][t] = f32x4{};
+      }
+    // sum over the clusters of z + lambda: the wave's problems in registers, the
+    // waves through LDS, in cluster order; then the s-update
+    auto consensus_s = [&]() {
+      f32x4 w[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) w[t] = f32x4{};
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        if (act[p]) {
+#pragma unroll
+          for (int t = 0; t < NT; ++t) w[t] += z[p][t] + lam[p][t];
+        }
+      }
+      if (!TWO) __syncthreads();
+      float4* mine = cons + wave * pitch + buf * NT * 64 + lane;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) mine[t * 64] = make_float4(w[t][0], w[t][1], w[t][2], w[t][3]);
+      __syncthreads();
+      const float4* src = cons + w0 * pitch + buf * NT * 64 + lane;
+      for (int i = 0; i < wps; ++i)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const float4 v = src[i * pitch + t * 64];
+          if (i == 0) w[t] = f32x4{v.x, v.y, v.z, v.w};
+          else w[t] += f32x4{v.x, v.y, v.z, v.w};
+        }
+      if (TWO) buf ^= 1;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          s[t][r] = (a.reg == 2) ? fminf(fmaxf(w[t][r] * a.invC, -a.box_r), a.box_r) : w[t][r] * a.inv_den;
+    };
+    consensus_s();
+    for (int it = 2; it <= a.T; ++it) {
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        f32x4 q[NT], bq[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            lam[p][t][r] = fmaf(a.gamma, z[p][t][r] - s[t][r], lam[p][t][r]);
+            q[t][r] = s[t][r] - lam[p][t][r];
+          }
+        syms_matvec<G, BLOCK>(A, p, q, bq, sg);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) z[p][t][r] = fmaf(a.rho, bq[t][r], yreg[p][t][r]);
+      }
+      consensus_s();
+    }
+    // outputs: the pair of lanes with a symbol's real and imaginary parts shares
+    // its users, two each of the four
+    if (wave == w0 && k < a.n_sc) {
+      const int n = n0 + j;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        float o[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[r] = swap_parts(s[t][r], 1.f);
+        const c32 e0 = im ? c32{o[2], s[t][2]} : c32{s[t][0], o[0]};
+        const c32 e1 = im ? c32{o[3], s[t][3]} : c32{s[t][1], o[1]};
+        if (n < a.n_sym) {
+          const size_t at = ((size_t)k * a.n_sym + n) * G + 16 * t + 4 * (lane >> 4) + 2 * im;
+          a.shat[at] = e0;
+          a.shat[at + 1] = e1;
+          if (a.hard) {
+            a.hard[at] = (uint8_t)(slice_dim(e0.re, a.kappa, a.L) + a.L * slice_dim(e0.im, a.kappa, a.L));
+            a.hard[at + 1] = (uint8_t)(slice_dim(e1.re, a.kappa, a.L) + a.L * slice_dim(e1.im, a.kappa, a.L));
+            if (near_threshold(e0.re, a.kappa, a.L, a.guard) || near_threshold(e0.im, a.kappa, a.L, a.guard) ||
+                near_threshold(e1.re, a.kappa, a.L, a.guard) || near_threshold(e1.im, a.kappa, a.L, a.guard))
+              fl |= 2;
+          }
+          if (nonfinite(e0) || nonfinite(e1)) fl |= 1;
+        }
+      }
+    }
+  }
+  return fl;
+}
+
+// ---------------------------------------------------------------------------
 // Algorithm 1, U x U branch (S >= U), FP32.  Group size G = U.
 // ---------------------------------------------------------------------------
 // HALF: 0 FP32 Gram, 1 / 2 split FP16 / BF16 Gram (mixed modes, U = 32, 64).
@@ -2079,13 +2348,13 @@ __device__ __forceinline__ c32 consensus_w(c32 wc, int buf, int ls, int u, int g
 // read from a.fac (every symbol's H_c^H y_c by the VALU pass); 3 as 2 with H
 // read from the packed FP16 channel; 4 (U = 32, FP32) as 1, and H also
 // written as the packed FP16 channel in the same launch.
-template <int G, int HALF, int INV, int STAGE>
+template <int G, int HALF, int INV, int STAGE, bool SYMS>
 __device__ __forceinline__ void admm_ul_body(const UlArgs& a);
 
-template <int G, int HALF, int INV, int STAGE>
-__global__ void __launch_bounds__(512) admm_ul_f32(UlArgs a) {
+template <int G, int HALF, int INV, int STAGE, bool SYMS = false>
+__global__ void __launch_bounds__(512, !SYMS ? 1 : G == 16 ? 4 : G == 32 ? 3 : 2) admm_ul_f32(UlArgs a) {
   a.blk = blockIdx.x;
-  admm_ul_body<G, HALF, INV, STAGE>(a);
+  admm_ul_body<G, HALF, INV, STAGE, SYMS>(a);
 }
 
 // Several frames of the same U in one launch (FP32, one-shot): frame f owns the
@@ -2096,18 +2365,22 @@ __global__ void __launch_bounds__(512) admm_ul_f32(UlArgs a) {
 // arguments.  One block of subcarriers per workgroup: with a persistent grid
 // (1024 workgroups in a loop over the blocks) eight uneven U = 16 frames took
 // 57 us instead of 55, the loop's registers costing a wave per SIMD.
-template <int G>
-__global__ void __launch_bounds__(512) admm_ul_f32_batch(UlBatch b) {
+// SYMS: some frame takes the column form of the iterations (symbol_columns).
+template <int G, bool SYMS>
+__global__ void __launch_bounds__(512, !SYMS ? 1 : G == 16 ? 4 : G == 32 ? 3 : 2) admm_ul_f32_batch(UlBatch b) {
   const int vb = blockIdx.x;
   int f = 0;
 #pragma unroll
   for (int i = 1; i < kMaxBatch; ++i) f += (b.first[i] <= vb) ? 1 : 0;
   UlArgs a = b.f[f];
   a.blk = vb - b.first[f];
-  admm_ul_body<G, 0, 0, 0>(a);
+  if constexpr (SYMS) {
+    if (symbol_columns(G, a.n_sym, a.C)) return admm_ul_body<G, 0, 0, 0, true>(a);
+  }
+  admm_ul_body<G, 0, 0, 0, false>(a);
 }
 
-template <int G, int HALF, int INV, int STAGE>
+template <int G, int HALF, int INV, int STAGE, bool SYMS>
 __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
   constexpr int P = 64 / G;
   constexpr bool RESIDENT = (STAGE == 2 || STAGE == 3);   // iterations against stored factors
@@ -2294,6 +2567,29 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
 #pragma unroll
       for (int v = 0; v < G; ++v)
         if (v >= u) a.fac[fo + (size_t)(v * (v + 1) / 2 + u)] = A[v];
+    }
+    return;
+  }
+
+  if constexpr (SYMS) {
+    if constexpr (LAZY) {
+      // 2 D - D S D
+      static_for<16>([&](auto vc) {
+        constexpr int v = decltype(vc)::value;
+        const float sc = -pvl * bcast16<v>(pvl);
+        A[v] = c32{fmaf(sc, A[v].re, u == v ? 2.f * pvl : 0.f), sc * A[v].im};
+      });
+    }
+    rows_to_operands<G>(A);
+    const int fl = syms_iterate<G, BLOCKS || BLOCKS64>(a, A, lane, wave, reinterpret_cast<float4*>(sm.stage));
+    if (a.flags) {
+      const int bits = group_flags<64>(fl, 0);
+      const int lead = wave * P;
+      const int kw = a.blk * a.sc_per_block + lead / a.Cp;
+      if (lead % a.Cp == 0 && lane == 0 && kw < a.n_sc) {
+        a.flags[kw] = bits;
+        if ((bits & kStatusReslice) && a.any) *a.any = a.epoch;
+      }
     }
     return;
   }
@@ -2948,7 +3244,11 @@ static hipError_t launch(K kernel, const Args& a, int nw, hipStream_t st) {
 
 template <int G, int HALF, int INV>
 static hipError_t launch_stage(const UlArgs& a, int nw, hipStream_t st, int stage) {
-  return stage == 1 ? launch(admm_ul_f32<G, HALF, INV, 1>, a, nw, st) : launch(admm_ul_f32<G, HALF, INV, 0>, a, nw, st);
+  if (stage == 1) return launch(admm_ul_f32<G, HALF, INV, 1>, a, nw, st);
+  if constexpr (HALF == 0 && G >= 16) {
+    if (symbol_columns(G, a.n_sym, a.C)) return launch(admm_ul_f32<G, 0, 0, 0, true>, a, nw, st);
+  }
+  return launch(admm_ul_f32<G, HALF, INV, 0>, a, nw, st);
 }
 
 hipError_t launch_factor_pack_u32(const UlArgs& a, int nw, hipStream_t st) {
@@ -2988,11 +3288,14 @@ hipError_t launch_admm_ul_mixed(const UlArgs& a, int U, int half, int inv, int n
 hipError_t launch_admm_ul_f32_batch(const UlBatch& b, int U, int nw, int grid, hipStream_t st) {
   if (b.n < 1 || grid == 0) return hipSuccess;
   const dim3 g((unsigned)grid), blk((unsigned)(64 * nw));
+  bool syms = false;
+  for (int i = 0; i < b.n; ++i) syms = syms || symbol_columns(U, b.f[i].n_sym, b.f[i].C);
+  const auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, blk, smem_bytes(nw), st, b); };
   switch (U) {
-    case 8: hipLaunchKernelGGL(admm_ul_f32_batch<8>, g, blk, smem_bytes(nw), st, b); break;
-    case 16: hipLaunchKernelGGL(admm_ul_f32_batch<16>, g, blk, smem_bytes(nw), st, b); break;
-    case 32: hipLaunchKernelGGL(admm_ul_f32_batch<32>, g, blk, smem_bytes(nw), st, b); break;
-    case 64: hipLaunchKernelGGL(admm_ul_f32_batch<64>, g, blk, smem_bytes(nw), st, b); break;
+    case 8: run(admm_ul_f32_batch<8, false>); break;
+    case 16: syms ? run(admm_ul_f32_batch<16, true>) : run(admm_ul_f32_batch<16, false>); break;
+    case 32: syms ? run(admm_ul_f32_batch<32, true>) : run(admm_ul_f32_batch<32, false>); break;
+    case 64: syms ? run(admm_ul_f32_batch<64, true>) : run(admm_ul_f32_batch<64, false>); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

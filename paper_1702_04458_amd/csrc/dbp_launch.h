@@ -99,6 +99,17 @@ struct FixBatch {
 static_assert(sizeof(UlBatch) <= 4096 && sizeof(FixBatch) <= 4096, "kernel argument blocks exceed 4 KiB");
 
 size_t smem_bytes(int nw);
+// Whether a detection call takes its symbols as matrix columns, eight at a time
+// (syms_iterate).  The columns cost the same for one symbol as for eight, the
+// vector form a constant per symbol; measured per call with 1, the line's number,
+// 7, 8 and 9 symbols (vector | columns, us):
+//   U = 16 (19200 subcarriers, B = 128, C = 8)  142 290 393 429 474 | 291 271 267 270 431   from 4
+//   U = 32 (9536 subcarriers, B = 256, C = 8)   272 609 783 867 946 | 540 543 544 549 845   from 5
+//   U = 64 (1192 subcarriers, B = 512, C = 8)   259 413 712 788 861 | 396 398 403 403 577   from 3
+// The 64 / U problems of a wave must be clusters of one subcarrier.
+__host__ __device__ inline bool symbol_columns(int U, int n_sym, int C) {
+  return U >= 16 && n_sym >= (U == 16 ? 4 : U == 32 ? 5 : 3) && C > 32 / U;
+}
 // one launch of grid workgroups (nw waves each; the sum of the frames' blocks) over all frames of b
 hipError_t launch_admm_ul_f32_batch(const UlBatch& b, int U, int nw, int grid, hipStream_t st);
 // FP64 re-slice of the flagged subcarriers of every frame of b
