@@ -12,6 +12,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "dbp_device.h"
 #include "dbp_launch.h"
 
@@ -2081,7 +2083,8 @@ __device__ __forceinline__ c32 consensus_w(c32 wc, int buf, int ls, int u, int g
 // cycles for eight symbols (256 cycles each).  Measured, 9536 subcarriers at
 // B = 256, U = 32, C = 8, T = 5: seven symbols 783 -> 544 us, fourteen 1370 -> 852.
 // Registers: U = 32 capped at 168 (three waves per SIMD; 169 and two: 626 us for
-// seven symbols), U = 16 at 128.
+// seven symbols), U = 16 at 128.  Against stored factors (the same sizes) seven
+// symbols 687 -> 370 us and fourteen 1288 -> 677.
 // ---------------------------------------------------------------------------
 
 // [Xr | Xi] -> [Xi | Xr], the first half times sg and the second times -sg (the
@@ -2091,7 +2094,9 @@ __device__ __forceinline__ float swap_parts(float x, float sg) {
 }
 
 // H_c^H y_c of symbols n0 .. n0 + 7 for the problems of the wave (zero past n_sym).
-template <int G>
+// H16: H from the packed FP16 channel, widened, the tile's power-of-two scale
+// applied at the end (exact).
+template <int G, bool H16>
 __device__ __forceinline__ void syms_hy(const UlArgs& a, int n0, f32x4 (&hy)[64 / G][G / 16], int lane, int wave) {
   constexpr int P = 64 / G, NT = G / 16;
   const int q = lane >> 4, col = lane & 15, j = col & 7;
@@ -2105,15 +2110,18 @@ __device__ __forceinline__ void syms_hy(const UlArgs& a, int n0, f32x4 (&hy)[64 
     const int ls = lp / a.Cp, c = lp % a.Cp;
     const int k = a.blk * a.sc_per_block + ls;
     const bool act = (k < a.n_sc) && (c < a.C);
-    const c32* Hp = act ? a.H + (size_t)k * a.B * G + (size_t)c * a.S * G : a.H;
+    const size_t ho = act ? (size_t)k * a.B * G + (size_t)c * a.S * G : 0;
     const c32* yp = act ? a.y + ((size_t)k * a.n_sym + n0) * a.B + (size_t)c * a.S : a.y;
-    hrs[p] = __builtin_amdgcn_make_buffer_rsrc(const_cast<c32*>(Hp), 0, act ? a.S * G * 8 : 0, kBufferWord3);
+    if constexpr (H16)
+      hrs[p] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(a.H16 + ho), 0, act ? a.S * G * 4 : 0, kBufferWord3);
+    else
+      hrs[p] = __builtin_amdgcn_make_buffer_rsrc(const_cast<c32*>(a.H + ho), 0, act ? a.S * G * 8 : 0, kBufferWord3);
     yrs[p] = __builtin_amdgcn_make_buffer_rsrc(const_cast<c32*>(yp), 0, act ? ((nj - 1) * a.B + a.S) * 8 : 0, kBufferWord3);
 #pragma unroll
     for (int t = 0; t < NT; ++t) hy[p][t] = hi[p][t] = f32x4{};
   }
   struct Rows {
-    c32 h[P][NT];
+    std::conditional_t<H16, uint32_t, c32> h[P][NT];
     float y[P];
   };
   auto fetch = [&](int s0, Rows& d) {
@@ -2123,9 +2131,13 @@ __device__ __forceinline__ void syms_hy(const UlArgs& a, int n0, f32x4 (&hy)[64 
 #pragma unroll
     for (int p = 0; p < P; ++p) {
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
-        d.h[p][t] = __builtin_bit_cast(
-            c32, __builtin_amdgcn_raw_buffer_load_b64(hrs[p], s * (G * 8) + t * 128 + col * 8, 0, 0));
+      for (int t = 0; t < NT; ++t) {
+        if constexpr (H16)
+          d.h[p][t] = __builtin_amdgcn_raw_buffer_load_b32(hrs[p], s * (G * 4) + t * 64 + col * 4, 0, 0);
+        else
+          d.h[p][t] = __builtin_bit_cast(
+              c32, __builtin_amdgcn_raw_buffer_load_b64(hrs[p], s * (G * 8) + t * 128 + col * 8, 0, 0));
+      }
       d.y[p] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(yrs[p], yo, 0, 0));
     }
   };
@@ -2134,9 +2146,13 @@ __device__ __forceinline__ void syms_hy(const UlArgs& a, int n0, f32x4 (&hy)[64 
     for (int p = 0; p < P; ++p) {
       const float ys = swap_parts(d.y[p], sg);
 #pragma unroll
-      for (int t = 0; t < NT; ++t) hy[p][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.h[p][t].re, d.y[p], hy[p][t], 0, 0, 0);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) hi[p][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(d.h[p][t].im, ys, hi[p][t], 0, 0, 0);
+      for (int t = 0; t < NT; ++t) {
+        c32 h;
+        if constexpr (H16) h = widen_h16(d.h[p][t]);
+        else h = d.h[p][t];
+        hy[p][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(h.re, d.y[p], hy[p][t], 0, 0, 0);
+        hi[p][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(h.im, ys, hi[p][t], 0, 0, 0);
+      }
     }
   };
   Rows d0, d1;
@@ -2151,9 +2167,20 @@ __device__ __forceinline__ void syms_hy(const UlArgs& a, int n0, f32x4 (&hy)[64 
   }
   if (s0 < a.S) accumulate(d0);
 #pragma unroll
-  for (int p = 0; p < P; ++p)
+  for (int p = 0; p < P; ++p) {
+    float scale = 1.f;
+    if constexpr (H16) {
+      const int lp = wave * P + p;
+      const int ls = lp / a.Cp, c = lp % a.Cp;
+      const int k = a.blk * a.sc_per_block + ls;
+      scale = (k < a.n_sc && c < a.C) ? a.hscale[(size_t)k * a.C + c] : 0.f;
+    }
 #pragma unroll
-    for (int t = 0; t < NT; ++t) hy[p][t] += hi[p][t];
+    for (int t = 0; t < NT; ++t) {
+      hy[p][t] += hi[p][t];
+      if constexpr (H16) hy[p][t] *= scale;
+    }
+  }
 }
 
 // The rows of the lane layout (lane 16 g + i: row i of lane group g) as operands:
@@ -2226,8 +2253,9 @@ __device__ __forceinline__ void syms_matvec(const c32 (&A)[G], int p, const f32x
 // The iterations of all symbols.  A: the factors as operands; cons: the waves'
 // stage buffers.  All problems of a wave belong to one subcarrier (Cp >= 64 / G).
 // Returns the status bits of the wave's outputs.
-template <int G, bool BLOCK>
-__device__ __forceinline__ int syms_iterate(const UlArgs& a, const c32 (&A)[G], int lane, int wave, float4* cons) {
+template <int G, bool BLOCK, bool H16>
+__device__ __forceinline__ int syms_iterate(const UlArgs& a, const c32 (&A)[G], int lane, int wave, float4* cons,
+                                            float guard) {
   constexpr int P = 64 / G, NT = G / 16, pitch = kStageWave / 2;
   constexpr bool TWO = 2 * NT * 64 <= pitch;   // two consensus buffers in turn (U = 64: one, and a second barrier)
   const int col = lane & 15, j = col & 7, im = col >> 3;
@@ -2243,7 +2271,7 @@ __device__ __forceinline__ int syms_iterate(const UlArgs& a, const c32 (&A)[G], 
     f32x4 z[P][NT], lam[P][NT], yreg[P][NT], s[NT];
     {
       f32x4 hy[P][NT];
-      syms_hy<G>(a, n0, hy, lane, wave);
+      syms_hy<G, H16>(a, n0, hy, lane, wave);
 #pragma unroll
       for (int p = 0; p < P; ++p) syms_matvec<G, BLOCK>(A, p, hy[p], yreg[p], sg);
     }
@@ -2325,8 +2353,8 @@ __device__ __forceinline__ int syms_iterate(const UlArgs& a, const c32 (&A)[G], 
           if (a.hard) {
             a.hard[at] = (uint8_t)(slice_dim(e0.re, a.kappa, a.L) + a.L * slice_dim(e0.im, a.kappa, a.L));
             a.hard[at + 1] = (uint8_t)(slice_dim(e1.re, a.kappa, a.L) + a.L * slice_dim(e1.im, a.kappa, a.L));
-            if (near_threshold(e0.re, a.kappa, a.L, a.guard) || near_threshold(e0.im, a.kappa, a.L, a.guard) ||
-                near_threshold(e1.re, a.kappa, a.L, a.guard) || near_threshold(e1.im, a.kappa, a.L, a.guard))
+            if (near_threshold(e0.re, a.kappa, a.L, guard) || near_threshold(e0.im, a.kappa, a.L, guard) ||
+                near_threshold(e1.re, a.kappa, a.L, guard) || near_threshold(e1.im, a.kappa, a.L, guard))
               fl |= 2;
           }
           if (nonfinite(e0) || nonfinite(e1)) fl |= 1;
@@ -2466,7 +2494,9 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
       for (int i = 0; i < NQ; ++i)
         tq[pp][i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(frs, (i * 64 + lane) * 16, 0, 0));
     }
-    if constexpr (STAGE == 3)
+    if constexpr (SYMS)
+      (void)hy0;
+    else if constexpr (STAGE == 3)
       hy0 = cluster_hy_direct<G, true>(a, k, c, 0, u, active);
     else
       hy0 = cluster_pass<G, false>(a.H, a.y, A, k, c, 0, u, g, lane, wave, active, a.B, a.S, G, a.n_sym, sm);
@@ -2571,29 +2601,6 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
     return;
   }
 
-  if constexpr (SYMS) {
-    if constexpr (LAZY) {
-      // 2 D - D S D
-      static_for<16>([&](auto vc) {
-        constexpr int v = decltype(vc)::value;
-        const float sc = -pvl * bcast16<v>(pvl);
-        A[v] = c32{fmaf(sc, A[v].re, u == v ? 2.f * pvl : 0.f), sc * A[v].im};
-      });
-    }
-    rows_to_operands<G>(A);
-    const int fl = syms_iterate<G, BLOCKS || BLOCKS64>(a, A, lane, wave, reinterpret_cast<float4*>(sm.stage));
-    if (a.flags) {
-      const int bits = group_flags<64>(fl, 0);
-      const int lead = wave * P;
-      const int kw = a.blk * a.sc_per_block + lead / a.Cp;
-      if (lead % a.Cp == 0 && lane == 0 && kw < a.n_sc) {
-        a.flags[kw] = bits;
-        if ((bits & kStatusReslice) && a.any) *a.any = a.epoch;
-      }
-    }
-    return;
-  }
-
   // FP64 factor rule (mixed modes, FP32 inverse): kappa_hat = tr(B_c)
   // ||B_c^{-1}||_F bounds the condition number kappa_2(B_c) from above (the
   // largest eigenvalue is at most the trace, and ||B_c^{-1}||_2 at most the
@@ -2617,6 +2624,45 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
       const float kh = (trg + (float)G * a.rho) * sqrtf(f2);
       if (u == 0) cond_slot[ls * a.Cp + c] = active ? kh : 0.f;
     }
+  }
+
+  if constexpr (SYMS) {
+    const int lead = wave * P;   // the wave's first problem
+    const int kw = a.blk * a.sc_per_block + lead / a.Cp;
+    int fl = 0;
+    if constexpr (COND) {
+      if (a.cond_max != 0.f) {
+        __syncthreads();
+        const float* kc = cond_slot + lead / a.Cp * a.Cp;
+        float km = 0.f;
+        bool bad = a.cond_max < 0.f;
+        for (int cc = 0; cc < a.C; ++cc) {
+          bad = bad || !(kc[cc] <= a.cond_max);   // NaN and infinity fail the comparison
+          km = fmaxf(km, kc[cc]);
+        }
+        if (bad) fl |= kStatusReslice | kStatusIllcond;
+        guard = a.guard * fmaxf(1.f, km / a.cond_ref);
+      }
+    }
+    if constexpr (LAZY) {
+      // 2 D - D S D, each entry rounded once (the scales' product as a pair)
+      static_for<16>([&](auto vc) {
+        constexpr int v = decltype(vc)::value;
+        const float pv = bcast16<v>(pvl);
+        const float hi = -pvl * pv, lo = fmaf(-pvl, pv, -hi);
+        A[v] = c32{fmaf(hi, A[v].re, fmaf(lo, A[v].re, u == v ? 2.f * pvl : 0.f)), fmaf(hi, A[v].im, lo * A[v].im)};
+      });
+    }
+    rows_to_operands<G>(A);
+    fl |= syms_iterate<G, BLOCKS || BLOCKS64, STAGE == 3>(a, A, lane, wave, reinterpret_cast<float4*>(sm.stage), guard);
+    if (a.flags) {
+      const int bits = group_flags<64>(fl, 0);
+      if (lead % a.Cp == 0 && lane == 0 && kw < a.n_sc) {
+        a.flags[kw] = bits;
+        if ((bits & kStatusReslice) && a.any) *a.any = a.epoch;
+      }
+    }
+    return;
   }
 
   int buf = 0;
@@ -3245,8 +3291,8 @@ static hipError_t launch(K kernel, const Args& a, int nw, hipStream_t st) {
 template <int G, int HALF, int INV>
 static hipError_t launch_stage(const UlArgs& a, int nw, hipStream_t st, int stage) {
   if (stage == 1) return launch(admm_ul_f32<G, HALF, INV, 1>, a, nw, st);
-  if constexpr (HALF == 0 && G >= 16) {
-    if (symbol_columns(G, a.n_sym, a.C)) return launch(admm_ul_f32<G, 0, 0, 0, true>, a, nw, st);
+  if constexpr (INV == 0 && G >= 16) {
+    if (symbol_columns(G, a.n_sym, a.C)) return launch(admm_ul_f32<G, HALF, 0, 0, true>, a, nw, st);
   }
   return launch(admm_ul_f32<G, HALF, INV, 0>, a, nw, st);
 }
@@ -3301,12 +3347,18 @@ hipError_t launch_admm_ul_f32_batch(const UlBatch& b, int U, int nw, int grid, h
   return hipGetLastError();
 }
 
+template <int U, int STAGE>
+static hipError_t launch_resident(const UlArgs& a, int nw, hipStream_t st) {
+  if (symbol_columns(U, a.n_sym, a.C)) return launch(admm_ul_f32<U, 0, 0, STAGE, true>, a, nw, st);
+  return launch(admm_ul_f32<U, 0, 0, STAGE>, a, nw, st);
+}
+
 hipError_t launch_admm_ul_factored(const UlArgs& a, int U, int nw, hipStream_t st) {
   switch (U) {
     case 8: return launch(admm_ul_f32<8, 0, 0, 2>, a, nw, st);
-    case 16: return launch(admm_ul_f32<16, 0, 0, 2>, a, nw, st);
-    case 32: return launch(admm_ul_f32<32, 0, 0, 2>, a, nw, st);
-    case 64: return launch(admm_ul_f32<64, 0, 0, 2>, a, nw, st);
+    case 16: return launch_resident<16, 2>(a, nw, st);
+    case 32: return launch_resident<32, 2>(a, nw, st);
+    case 64: return launch_resident<64, 2>(a, nw, st);
   }
   return hipErrorInvalidValue;
 }
@@ -3314,9 +3366,9 @@ hipError_t launch_admm_ul_factored(const UlArgs& a, int U, int nw, hipStream_t s
 hipError_t launch_admm_ul_factored_h16(const UlArgs& a, int U, int nw, hipStream_t st) {
   switch (U) {
     case 8: return launch(admm_ul_f32<8, 0, 0, 3>, a, nw, st);
-    case 16: return launch(admm_ul_f32<16, 0, 0, 3>, a, nw, st);
-    case 32: return launch(admm_ul_f32<32, 0, 0, 3>, a, nw, st);
-    case 64: return launch(admm_ul_f32<64, 0, 0, 3>, a, nw, st);
+    case 16: return launch_resident<16, 3>(a, nw, st);
+    case 32: return launch_resident<32, 3>(a, nw, st);
+    case 64: return launch_resident<64, 3>(a, nw, st);
   }
   return hipErrorInvalidValue;
 }

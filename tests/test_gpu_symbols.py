@@ -105,3 +105,47 @@ def test_block_factors_of_correlated_channels(U, C, n_sym, corr, rho):
     ev = np.linalg.eigvalsh(np.swapaxes(Hc.conj(), -1, -2) @ Hc + rho * np.eye(U))
     kappa = (ev[..., -1] / ev[..., 0]).max()
     assert np.linalg.norm(s.cpu().numpy() - ref) <= max(1e-5, kappa * 2.0 ** -24) * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("U,C,S,n_sym", [(16, 3, 19, 4), (16, 8, 16, 9), (32, 3, 33, 5), (32, 8, 32, 9), (64, 1, 67, 3),
+                                         (64, 8, 64, 9)])
+@pytest.mark.parametrize("h16", [False, True])
+def test_symbols_of_a_static_channel(U, C, S, n_sym, h16):
+    """Against stored factors: the oracle's result, and for the packed channel, whose
+    rounding of H the oracle does not have, the results of one symbol at a time
+    (both within 1e-5 of the exact ones of the rounded channel, so 2e-5 apart)."""
+    say(f"[gpu] symbols against factors U={U} C={C} S={S} n_sym={n_sym} h16={h16}")
+    fr, H, y = frame(19, n_sym, S * C, U, U + S)
+    F = api.factor(H, C, 1.0)
+    if not h16:
+        s, h = api.detect_factored(H, F, y, fr.N0, C, qam=16)
+        ref = oracle(fr, C, 5)
+        assert np.linalg.norm(s.cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(ref)
+        assert np.array_equal(h.cpu().numpy(), O.slice_qam(ref, 16))
+        return
+    packed = api.pack_channel_h16(H, C)
+
+    def run(v):
+        return api.detect_factored_h16(packed, F, v, fr.N0, S * C, U, C, qam=16, hard=False)[0]
+
+    want = torch.cat([run(y[:, n:n + 1].contiguous()) for n in range(n_sym)], 1).cpu().numpy()
+    assert np.linalg.norm(run(y).cpu().numpy() - want) <= 2e-5 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("U,C,S", [(32, 3, 33), (64, 2, 64)])
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("rho", [1.0, 0.01])
+def test_symbols_in_mixed_precision(U, C, S, prec, rho):
+    """Mixed modes with the FP64 factor rule (S = U or close: on): the oracle's
+    decisions, the conditioning flags of a single symbol, and soft values within
+    the modes' 1e-3."""
+    say(f"[gpu] symbols mixed U={U} C={C} S={S} {prec} rho={rho}")
+    n_sym = 9
+    fr, H, y = frame(11, n_sym, S * C, U, U + S, snr=20.0)
+    s, h, st = api.detect(H, y, fr.N0, C, rho, qam=16, prec=prec, status=True)
+    _, _, st1 = api.detect(H, y[:, :1].contiguous(), fr.N0, C, rho, qam=16, prec=prec, status=True)
+    torch.cuda.synchronize()
+    ref = oracle(fr, C, 5, rho=rho)
+    assert np.linalg.norm(s.cpu().numpy() - ref) <= 1e-3 * np.linalg.norm(ref)
+    assert np.array_equal(h.cpu().numpy(), O.slice_qam(ref, 16))
+    assert torch.equal(st & 4, st1 & 4)
