@@ -2250,16 +2250,77 @@ __device__ __forceinline__ void syms_matvec(const c32 (&A)[G], int p, const f32x
   }
 }
 
+// Sum of w over the wps waves of a subcarrier through their stage buffers, in
+// cluster order.
+template <int G>
+__device__ __forceinline__ void syms_consensus(f32x4 (&w)[G / 16], float4* cons, int& buf, int lane, int wave, int wps) {
+  constexpr int NT = G / 16, pitch = kStageWave / 2;
+  constexpr bool TWO = 2 * NT * 64 <= pitch;   // two buffers in turn (U = 64: one, and a second barrier)
+  if (!TWO) __syncthreads();
+  float4* mine = cons + wave * pitch + buf * NT * 64 + lane;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) mine[t * 64] = make_float4(w[t][0], w[t][1], w[t][2], w[t][3]);
+  __syncthreads();
+  const float4* src = cons + wave / wps * wps * pitch + buf * NT * 64 + lane;
+  for (int i = 0; i < wps; ++i)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const float4 v = src[i * pitch + t * 64];
+      if (i == 0) w[t] = f32x4{v.x, v.y, v.z, v.w};
+      else w[t] += f32x4{v.x, v.y, v.z, v.w};
+    }
+  if (TWO) buf ^= 1;
+}
+
+// Outputs of symbols n0 .. n0 + 7 of subcarrier k: the pair of lanes with a
+// symbol's real and imaginary parts shares its users, two each of the four.
+// Returns the lane's status bits.
+template <int G>
+__device__ __forceinline__ int syms_store(const UlArgs& a, const f32x4 (&s)[G / 16], int k, int n0, int lane, float guard) {
+  const int im = (lane >> 3) & 1, n = n0 + (lane & 7);
+  int fl = 0;
+#pragma unroll
+  for (int t = 0; t < G / 16; ++t) {
+    float o[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) o[r] = swap_parts(s[t][r], 1.f);
+    const c32 e0 = im ? c32{o[2], s[t][2]} : c32{s[t][0], o[0]};
+    const c32 e1 = im ? c32{o[3], s[t][3]} : c32{s[t][1], o[1]};
+    if (n < a.n_sym) {
+      const size_t at = ((size_t)k * a.n_sym + n) * G + 16 * t + 4 * (lane >> 4) + 2 * im;
+      a.shat[at] = e0;
+      a.shat[at + 1] = e1;
+      if (a.hard) {
+        a.hard[at] = (uint8_t)(slice_dim(e0.re, a.kappa, a.L) + a.L * slice_dim(e0.im, a.kappa, a.L));
+        a.hard[at + 1] = (uint8_t)(slice_dim(e1.re, a.kappa, a.L) + a.L * slice_dim(e1.im, a.kappa, a.L));
+        if (near_threshold(e0.re, a.kappa, a.L, guard) || near_threshold(e0.im, a.kappa, a.L, guard) ||
+            near_threshold(e1.re, a.kappa, a.L, guard) || near_threshold(e1.im, a.kappa, a.L, guard))
+          fl |= 2;
+      }
+      if (nonfinite(e0) || nonfinite(e1)) fl |= 1;
+    }
+  }
+  return fl;
+}
+
+// The subcarrier's status word from the bits of its first wave.
+__device__ __forceinline__ void syms_flags(const UlArgs& a, int fl, int k, bool first, int lane) {
+  if (!a.flags) return;
+  const int bits = group_flags<64>(fl, 0);
+  if (first && lane == 0 && k < a.n_sc) {
+    a.flags[k] = bits;
+    if ((bits & kStatusReslice) && a.any) *a.any = a.epoch;
+  }
+}
+
 // The iterations of all symbols.  A: the factors as operands; cons: the waves'
 // stage buffers.  All problems of a wave belong to one subcarrier (Cp >= 64 / G).
 // Returns the status bits of the wave's outputs.
 template <int G, bool BLOCK, bool H16>
 __device__ __forceinline__ int syms_iterate(const UlArgs& a, const c32 (&A)[G], int lane, int wave, float4* cons,
                                             float guard) {
-  constexpr int P = 64 / G, NT = G / 16, pitch = kStageWave / 2;
-  constexpr bool TWO = 2 * NT * 64 <= pitch;   // two consensus buffers in turn (U = 64: one, and a second barrier)
-  const int col = lane & 15, j = col & 7, im = col >> 3;
-  const float sg = (im != 0) == BLOCK ? -1.f : 1.f;   // [-xi | xr], or with conjugated factors [xi | -xr]
+  constexpr int P = 64 / G, NT = G / 16;
+  const float sg = ((lane & 8) != 0) == BLOCK ? -1.f : 1.f;   // [-xi | xr], or with conjugated factors [xi | -xr]
   const int wps = a.Cp / P;                           // waves of a subcarrier
   const int w0 = wave / wps * wps;                    // the first of them
   const int k = a.blk * a.sc_per_block + wave / wps;
@@ -2295,20 +2356,7 @@ __device__ __forceinline__ int syms_iterate(const UlArgs& a, const c32 (&A)[G], 
           for (int t = 0; t < NT; ++t) w[t] += z[p][t] + lam[p][t];
         }
       }
-      if (!TWO) __syncthreads();
-      float4* mine = cons + wave * pitch + buf * NT * 64 + lane;
-#pragma unroll
-      for (int t = 0; t < NT; ++t) mine[t * 64] = make_float4(w[t][0], w[t][1], w[t][2], w[t][3]);
-      __syncthreads();
-      const float4* src = cons + w0 * pitch + buf * NT * 64 + lane;
-      for (int i = 0; i < wps; ++i)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const float4 v = src[i * pitch + t * 64];
-          if (i == 0) w[t] = f32x4{v.x, v.y, v.z, v.w};
-          else w[t] += f32x4{v.x, v.y, v.z, v.w};
-        }
-      if (TWO) buf ^= 1;
+      syms_consensus<G>(w, cons, buf, lane, wave, wps);
 #pragma unroll
       for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -2335,32 +2383,7 @@ __device__ __forceinline__ int syms_iterate(const UlArgs& a, const c32 (&A)[G], 
       }
       consensus_s();
     }
-    // outputs: the pair of lanes with a symbol's real and imaginary parts shares
-    // its users, two each of the four
-    if (wave == w0 && k < a.n_sc) {
-      const int n = n0 + j;
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        float o[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) o[r] = swap_parts(s[t][r], 1.f);
-        const c32 e0 = im ? c32{o[2], s[t][2]} : c32{s[t][0], o[0]};
-        const c32 e1 = im ? c32{o[3], s[t][3]} : c32{s[t][1], o[1]};
-        if (n < a.n_sym) {
-          const size_t at = ((size_t)k * a.n_sym + n) * G + 16 * t + 4 * (lane >> 4) + 2 * im;
-          a.shat[at] = e0;
-          a.shat[at + 1] = e1;
-          if (a.hard) {
-            a.hard[at] = (uint8_t)(slice_dim(e0.re, a.kappa, a.L) + a.L * slice_dim(e0.im, a.kappa, a.L));
-            a.hard[at + 1] = (uint8_t)(slice_dim(e1.re, a.kappa, a.L) + a.L * slice_dim(e1.im, a.kappa, a.L));
-            if (near_threshold(e0.re, a.kappa, a.L, guard) || near_threshold(e0.im, a.kappa, a.L, guard) ||
-                near_threshold(e1.re, a.kappa, a.L, guard) || near_threshold(e1.im, a.kappa, a.L, guard))
-              fl |= 2;
-          }
-          if (nonfinite(e0) || nonfinite(e1)) fl |= 1;
-        }
-      }
-    }
+    if (wave == w0 && k < a.n_sc) fl |= syms_store<G>(a, s, k, n0, lane, guard);
   }
   return fl;
 }
@@ -2655,13 +2678,7 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
     }
     rows_to_operands<G>(A);
     fl |= syms_iterate<G, BLOCKS || BLOCKS64, STAGE == 3>(a, A, lane, wave, reinterpret_cast<float4*>(sm.stage), guard);
-    if (a.flags) {
-      const int bits = group_flags<64>(fl, 0);
-      if (lead % a.Cp == 0 && lane == 0 && kw < a.n_sc) {
-        a.flags[kw] = bits;
-        if ((bits & kStatusReslice) && a.any) *a.any = a.epoch;
-      }
-    }
+    syms_flags(a, fl, kw, lead % a.Cp == 0, lane);
     return;
   }
 
@@ -2739,12 +2756,95 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
   }
 }
 
+// Algorithm 2 over the symbols as columns.  A: the Grams as operands.  x, r and p
+// are the same on every wave of the subcarrier; alpha and beta are scalars of a
+// column pair.
+template <int G>
+__device__ __forceinline__ int syms_cg(const UlArgs& a, const c32 (&A)[G], int lane, int wave, float4* cons) {
+  constexpr int P = 64 / G, NT = G / 16;
+  const float sg = (lane & 8) ? 1.f : -1.f;   // [-xi | xr]
+  const int wps = a.Cp / P, w0 = wave / wps * wps;
+  const int k = a.blk * a.sc_per_block + wave / wps;
+  int fl = 0, buf = 0;
+  bool act[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) act[p] = k < a.n_sc && (wave - w0) * P + p < a.C;
+  // sum of v . w over the users and the two parts of a symbol
+  auto dot = [&](const f32x4 (&v)[NT], const f32x4 (&w)[NT]) {
+    float d[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      d[t] = fmaf(v[t][0], w[t][0], v[t][1] * w[t][1]) + fmaf(v[t][2], w[t][2], v[t][3] * w[t][3]);
+    float e = d[0];
+#pragma unroll
+    for (int t = 1; t < NT; ++t) e += d[t];
+    return pair_sum<32>(pair_sum<16>(e + swap_parts(e, 1.f)));
+  };
+  for (int n0 = 0; n0 < a.n_sym; n0 += 8) {
+    f32x4 x[NT], r[NT], pv[NT];
+    {
+      f32x4 hy[P][NT];
+      syms_hy<G, false>(a, n0, hy, lane, wave);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) r[t] = x[t] = f32x4{};
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        if (act[p]) {
+#pragma unroll
+          for (int t = 0; t < NT; ++t) r[t] += hy[p][t];
+        }
+      }
+    }
+    syms_consensus<G>(r, cons, buf, lane, wave, wps);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) pv[t] = r[t];
+    float rr = dot(r, r);
+    for (int it = 1; it <= a.T; ++it) {
+      f32x4 e[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) e[t] = f32x4{};
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        if (act[p]) {
+          f32x4 wc[NT];
+          syms_matvec<G, false>(A, p, pv, wc, sg);
+#pragma unroll
+          for (int t = 0; t < NT; ++t) e[t] += wc[t];
+        }
+      }
+      syms_consensus<G>(e, cons, buf, lane, wave, wps);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e[t][i] = fmaf(a.rho, pv[t][i], e[t][i]);
+      const float pe = dot(pv, e);
+      const float alpha = (rr > 0.f) ? rr * __builtin_amdgcn_rcpf(pe) : 0.f;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          x[t][i] = fmaf(alpha, pv[t][i], x[t][i]);
+          r[t][i] = fmaf(-alpha, e[t][i], r[t][i]);
+        }
+      const float rr_new = dot(r, r);
+      const float beta = (rr > 0.f) ? rr_new * __builtin_amdgcn_rcpf(rr) : 0.f;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pv[t][i] = fmaf(beta, pv[t][i], r[t][i]);
+      rr = rr_new;
+    }
+    if (wave == w0 && k < a.n_sc) fl |= syms_store<G>(a, x, k, n0, lane, a.guard);
+  }
+  return fl;
+}
+
 // ---------------------------------------------------------------------------
 // Algorithm 2 (decentralized CG), FP32.  Each cluster keeps its own copy of
 // x, r, p (the broadcast-w variant) and contributes w_c = H_c^H H_c p through
 // its local Gram G_c held in registers (one matvec per iteration).
 // ---------------------------------------------------------------------------
-template <int G>
+template <int G, bool SYMS = false>
 __global__ void __launch_bounds__(512) dcg_ul_f32(UlArgs a) {
   a.blk = blockIdx.x;
   constexpr int P = 64 / G;
@@ -2779,6 +2879,14 @@ __global__ void __launch_bounds__(512) dcg_ul_f32(UlArgs a) {
                                reinterpret_cast<float*>(sm.stage + wave * kStageWave));
   else
     hy0 = cluster_pass<G, true>(a.H, a.y, A, k, c, 0, u, g, lane, wave, active, a.B, a.S, G, a.n_sym, sm);
+
+  if constexpr (SYMS) {
+    rows_to_operands<G>(A);
+    const int fl = syms_cg<G>(a, A, lane, wave, reinterpret_cast<float4*>(sm.stage));
+    const int lead = wave * P;   // the wave's first problem
+    syms_flags(a, fl, a.blk * a.sc_per_block + lead / a.Cp, lead % a.Cp == 0, lane);
+    return;
+  }
 
   int buf = 0;
   int fl = 0;   // status bits of this lane's outputs (bit 0 non-finite, bit 1 re-slice)
@@ -3389,12 +3497,17 @@ hipError_t launch_scan_nonfinite(const float* x, size_t floats_per_sc, int n_sc,
   return hipGetLastError();
 }
 
+template <int U>
+static hipError_t launch_dcg(const UlArgs& a, int nw, hipStream_t st) {
+  return symbol_columns(U, a.n_sym, a.C) ? launch(dcg_ul_f32<U, true>, a, nw, st) : launch(dcg_ul_f32<U>, a, nw, st);
+}
+
 hipError_t launch_dcg_ul_f32(const UlArgs& a, int U, int nw, hipStream_t st) {
   switch (U) {
     case 8: return launch(dcg_ul_f32<8>, a, nw, st);
-    case 16: return launch(dcg_ul_f32<16>, a, nw, st);
-    case 32: return launch(dcg_ul_f32<32>, a, nw, st);
-    case 64: return launch(dcg_ul_f32<64>, a, nw, st);
+    case 16: return launch_dcg<16>(a, nw, st);
+    case 32: return launch_dcg<32>(a, nw, st);
+    case 64: return launch_dcg<64>(a, nw, st);
   }
   return hipErrorInvalidValue;
 }

@@ -114,6 +114,10 @@ size_t smem_bytes(int nw);
 // and with the split FP16 Gram, U = 32 and 64:
 //   473 738 894 987 1081 | 659 607 612 611 881
 //   298 443 731 807 877 | 420 423 429 429 598
+// and by conjugate gradients:
+//   95 284 406 448 486 | 226 217 216 217 361
+//   174 566 759 863 956 | 409 412 422 425 724
+//   150 298 582 654 724 | 269 270 274 276 443
 // The 64 / U problems of a wave must be clusters of one subcarrier.
 __host__ __device__ inline bool symbol_columns(int U, int n_sym, int C) {
   return U >= 16 && n_sym >= (U == 16 ? 4 : U == 32 ? 5 : 3) && C > 32 / U;

@@ -52,6 +52,18 @@ def test_symbols_as_columns(U, C, S, n_sym, T, reg):
     assert not (st.cpu().numpy() & 1).any()
 
 
+@pytest.mark.parametrize("U,C,S,n_sym,T,reg", [c for c in CASES if c[5] != "box"])
+def test_symbols_as_columns_cg(U, C, S, n_sym, T, reg):
+    say(f"[gpu] symbols by CG U={U} C={C} S={S} n_sym={n_sym} T={T} {reg}")
+    fr, H, y = frame(21, n_sym, S * C, U, U + C + S)
+    s, h, st = api.detect(H, y, fr.N0, C, T=T, algo="cg", qam=16, reg=reg, status=True)
+    torch.cuda.synchronize()
+    ref = O.dcg_ul_frame(fr.H, fr.y, C, T, float(np.float32(fr.N0)), reg=reg)
+    assert np.linalg.norm(s.cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(ref)
+    assert np.array_equal(h.cpu().numpy(), O.slice_qam(ref, 16))
+    assert not (st.cpu().numpy() & 1).any()
+
+
 @pytest.mark.parametrize("U,C", [(16, 4), (32, 4), (64, 2)])
 def test_symbols_are_independent(U, C):
     """A symbol with infinities and NaN leaves the others' bits alone, and a
