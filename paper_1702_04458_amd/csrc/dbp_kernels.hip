@@ -1716,10 +1716,20 @@ __device__ __forceinline__ c32 combine_hy_u64(c32 e0, c32 e1, int h) {
   return c32{yr.lo + yr.hi, yi.lo + yi.hi};
 }
 
+// A cluster's S x 64 uplink block of a downlink problem, entry (antenna a, user w),
+// in either layout of H (zero past S).
+struct DlBlock64 {
+  __amdgpu_buffer_rsrc_t rs;
+  int S, sa, su;   // strides in bytes
+  __device__ __forceinline__ c32 at(int a, int w) const {
+    return __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(rs, a < S ? a * sa + w * su : (int)0x80000000u, 0, 0));
+  }
+};
+
 // INVERT: 0 the Gram (rows of G in A), 1 its block factors, 2 rows of the inverse.
-template <int INVERT>
+template <int INVERT, bool DL = false>
 __device__ __forceinline__ c32 gram_mfma_u64(const UlArgs& a, c32 (&A)[64], int lane, int wave, float* line,
-                                             float* stage) {
+                                             float* stage, const DlBlock64* dl = nullptr) {
   const int h = lane >> 5, col = lane & 31;
   f32x16 re[2][2], im[2][2];
   c32 hy0 = cz(), hy1 = cz();
@@ -1743,6 +1753,12 @@ __device__ __forceinline__ c32 gram_mfma_u64(const UlArgs& a, c32 (&A)[64], int 
   };
   auto fetch = [&](int s0, Rows& d) {
     const int s = s0 + h;   // row s, columns col and 32 + col: bytes 512 s + 8 col (+ 256)
+    if constexpr (DL) {
+      d.x0 = dl->at(col, s);
+      d.x1 = dl->at(32 + col, s);
+      d.y = cz();
+      return;
+    }
     d.x0 = __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(hrs, s * 512 + col * 8, 0, 0));
     d.x1 = __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(hrs, s * 512 + 256 + col * 8, 0, 0));
     d.y = __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(yrs, s * 8, 0, 0));
@@ -3007,12 +3023,30 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
   // share the sweep and the products A_c^{-1} r.
   constexpr bool ASPLIT = LATE_H;
   constexpr int NR = ASPLIT ? 8 : SG;      // entries of A_c per lane
-  c32 hcol[SG], hrow[RS], A[NR];
+  // U = 64, S > 32: two copies of the 64 x 64 block beside A_c do not fit a lane's
+  // registers (535 spilled, 1.5 KB of scratch per lane); H is read again for
+  // every product instead, A_c is formed and inverted on the matrix cores.
+  // B = 512, C = 8, S = 64, 1200 subcarriers, T = 5: 8.82 -> 1.29 ms; B = 92,
+  // C = 2, S = 46, 1981 subcarriers: 3.01 -> 0.50 ms.
+  constexpr bool STREAM = (G == 64 && SG == 64 && !BUDGET);
+  constexpr int kUnroll = STREAM ? 4 : 16;   // (STREAM: 16 loads in flight)
+  DlBlock64 hb{};
+  if constexpr (STREAM) {
+    const size_t ho = active ? (size_t)k * a.B * G + (dl_layout ? (size_t)c * S : (size_t)c * S * G) : 0;
+    hb.rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<c32*>(a.H + ho), 0,
+                                              active ? (dl_layout ? (63 * a.B + S) * 8 : S * 512) : 0, kBufferWord3);
+    hb.S = S;
+    hb.sa = dl_layout ? 8 : 512;
+    hb.su = dl_layout ? a.B * 8 : 8;
+  }
+  c32 hcol[STREAM ? 1 : SG], hrow[STREAM ? 1 : RS], A[NR];
+  if constexpr (!STREAM) {
 #pragma unroll
-  for (int i = 0; i < SG; ++i) hcol[i] = (active && i < S) ? Hk[(size_t)i * sa + (size_t)u * su] : cz();
+    for (int i = 0; i < SG; ++i) hcol[i] = (active && i < S) ? Hk[(size_t)i * sa + (size_t)u * su] : cz();
+  }
 #pragma unroll
   for (int i = 0; i < NR; ++i) A[i] = cz();
-  if constexpr (!LATE_H) {
+  if constexpr (!LATE_H && !STREAM) {
 #pragma unroll
     for (int i = 0; i < RS; ++i) hrow[i] = (active && ra < S) ? Hk[(size_t)ra * sa + (size_t)(r0 + i) * su] : cz();
   }
@@ -3065,6 +3099,20 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
     }
     // (the vector sweep in both forms: a budget that never binds changes nothing)
     shift_invert_s16<false>(T, irho, irho, S, A, lane, line);
+  } else if constexpr (STREAM) {
+    UlArgs ua{};
+    ua.H = a.H;
+    ua.y = a.H;   // (not read)
+    ua.n_sc = a.n_sc;
+    ua.B = a.B;
+    ua.C = a.C;
+    ua.Cp = a.Cp;
+    ua.S = 64;    // rows of H_c: the users
+    ua.sc_per_block = a.sc_per_block;
+    ua.rho = irho;
+    ua.blk = blockIdx.x;
+    gram_mfma_u64<2, true>(ua, A, lane, wave, reinterpret_cast<float*>(line),
+                           reinterpret_cast<float*>(sm.stage + wave * kStageWave), &hb);
   } else {
     gram_into(A);
     if constexpr (BUDGET) {
@@ -3142,12 +3190,15 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
       } else {
         bl[bw] = v;
         wave_lds_sync();
-#pragma unroll
+#pragma unroll kUnroll
         for (int v0 = 0; v0 < RS; v0 += 4) {
           c32 vv[4];
           lds_read_vec<4>(bl + br + v0, vv);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) cmacc(acc, hrow[v0 + i], vv[i]);
+          for (int i = 0; i < 4; ++i) {
+            if constexpr (STREAM) cmacc(acc, hb.at(u, v0 + i), vv[i]);
+            else cmacc(acc, hrow[v0 + i], vv[i]);
+          }
         }
         wave_lds_sync();
       }
@@ -3174,12 +3225,15 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
         bl[bw] = xa;
         wave_lds_sync();
         c32 m = cz();
-#pragma unroll
+#pragma unroll kUnroll
         for (int v0 = 0; v0 < SG; v0 += 4) {
           c32 xv[4];
           lds_read_vec<4>(bl + v0, xv);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) cmac(m, hcol[v0 + i], xv[i]);
+          for (int i = 0; i < 4; ++i) {
+            if constexpr (STREAM) cmac(m, hb.at(v0 + i, u), xv[i]);
+            else cmac(m, hcol[v0 + i], xv[i]);
+          }
         }
         wave_lds_sync();
         const c32 q = hhv(m);
@@ -3266,12 +3320,15 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
       } else {
         bl[bw] = x;
         wave_lds_sync();
-#pragma unroll
+#pragma unroll kUnroll
         for (int v0 = 0; v0 < SG; v0 += 4) {
           c32 xv[4];
           lds_read_vec<4>(bl + v0, xv);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) cmac(m, hcol[v0 + i], xv[i]);
+          for (int i = 0; i < 4; ++i) {
+            if constexpr (STREAM) cmac(m, hb.at(v0 + i, u), xv[i]);
+            else cmac(m, hcol[v0 + i], xv[i]);
+          }
         }
         wave_lds_sync();
       }
