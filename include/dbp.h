@@ -187,8 +187,8 @@ int dbp_detect_admm_noalloc(const void* H, const void* y, void* s_hat, uint8_t* 
  * Other arguments (hard decisions, status and workspace included),
  * requirements and errors are those of dbp_detect_admm; the FP64 re-slice
  * recomputes flagged subcarriers from H (the FP32 guards, for FP32 factors).
- * The result equals dbp_detect_admm up to the rounding of H_c^H y_c, which
- * the factored path forms on the vector units. */
+ * The result equals dbp_detect_admm up to FP32 rounding (of H_c^H y_c, and of
+ * the inverse, which dbp_detect_admm keeps as block factors at U >= 32). */
 size_t dbp_factor_bytes(int n_sc, int U, int C);
 int dbp_factor_admm(const void* H, void* factors, int n_sc, int B, int U, int C,
                     float rho, int prec, void* stream);
