@@ -23,6 +23,8 @@ __device__ __forceinline__ c32 cz() { return c32{0.f, 0.f}; }
 __device__ __forceinline__ c32 cadd(c32 a, c32 b) { return c32{a.re + b.re, a.im + b.im}; }
 __device__ __forceinline__ c32 csub(c32 a, c32 b) { return c32{a.re - b.re, a.im - b.im}; }
 __device__ __forceinline__ c32 cscale(c32 a, float f) { return c32{a.re * f, a.im * f}; }
+// a 2^e
+__device__ __forceinline__ c32 cldexp(c32 a, int e) { return c32{ldexpf(a.re, e), ldexpf(a.im, e)}; }
 __device__ __forceinline__ c32 cmul(c32 a, c32 b) {
   return c32{a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }

@@ -2952,8 +2952,9 @@ __global__ void __launch_bounds__(512) dcg_ul_f32(UlArgs a) {
   }
 }
 
-// Inversions of one budgeted (P1) at most (one from a cold start, none to one
-// from the previous x-update's shift, see admm_dl_body).
+// Inversions of one budgeted (P1) at most (see admm_dl_body; an FP32 model of the
+// step over 6000 random problems, from a cold start each, needs two in 71 % of
+// them, one in 24 % and four at most).
 constexpr int kBudgetSteps = 12;
 
 // ---------------------------------------------------------------------------
@@ -2976,12 +2977,18 @@ constexpr int kBudgetSteps = 12;
 // and increasing in tau, and nearly linear), polished on the polynomial where
 // the series converges fast.  If the truncated tail of x is below FP32
 // rounding the x-update is done, with no inversion at all; otherwise M is
-// formed anew at tau_M + d and the step repeats.  The shift moves little from
-// one x-update to the next, so a product (about 45 instructions) replaces most
-// inversions (about 900): B=256 U=32 C=16, 1200 subcarriers, T=5, budgets
-// binding on half of the clusters: 754 us with Newton's method and a Gram and
-// an inversion per step (about 25 of them), 240 us in this form (3.7 times at
-// budgets of a third of the mean energy); its error against FP64 is unchanged.
+// formed anew at tau_M + d and the step repeats.  The powers run in units of
+// ||u_0|| and of the rate ||u_1|| / ||u_0||: g_6 falls with the eighth power of
+// the shift and would leave FP32 at amplitudes of H of 1e3 or 1e-6.  The tail
+// is estimated, not bounded: d^4 ||u_4|| with ||u_4|| taken as ||u_3||^2 / ||u_2||
+// (at most 1.33 times too small in the 6000 problems of kBudgetSteps).
+// The shift moves little from one x-update to the next, so a product (about 45
+// instructions) replaces most inversions (about 900): B=256 U=32 C=16, 1200
+// subcarriers, T=5, budgets binding on half of the clusters: 754 us with Newton's
+// method and a Gram and an inversion per step (about 25 of them), 225 us in this
+// form.  Relative error against FP64 at amplitudes of H of 1e-9 to 1e6 (rho fixed
+// or scaled along), budgets of 1e-30 to 0.9 of the free energy and rho of 1e-12 to
+// 1e12 on well-conditioned clusters: at most 8e-7, as at unit scale.
 template <int G, int SG, bool BUDGET = false>
 __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
   constexpr int P = 64 / G;
@@ -3254,42 +3261,65 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
         };
         bool need = active && dot(xa, xa) > Pc;
         const float sp = sqrtf(Pc);
+        if (need && sp == 0.f) {
+          xa = cz();
+          need = false;
+        }
         for (int it = 0; __ballot(need); ++it) {   // wave-uniform: products and inversions are wave operations
-          const c32 u0 = mul(r), u1 = mul(u0), u2 = mul(u1), u3 = mul(u2);
+          // u_j in units of 2^e0 and the shift in units of 2^-e1, so that every
+          // g_m is of order one whatever the scales of H, rho and P_c: 2^e0 is
+          // near ||M r||, 2^e1 near the rate ||M u_0|| / ||u_0|| (powers of two: exact)
+          c32 u0 = mul(r);
+          const int e0 = __builtin_amdgcn_frexp_expf(dot(u0, u0)) >> 1;
+          u0 = cldexp(u0, -e0);
+          c32 u1 = mul(u0);
+          const int e1 = __builtin_amdgcn_frexp_expf(dot(u0, u1));
+          u1 = cldexp(u1, -e1);
+          const c32 u2 = cldexp(mul(u1), -e1), u3 = cldexp(mul(u2), -e1);
           const float g0 = dot(u0, u0), g1 = dot(u0, u1), g2 = dot(u1, u1), g3 = dot(u1, u2), g4 = dot(u2, u2),
                       g5 = dot(u2, u3), g6 = dot(u3, u3);
+          const float sh = ldexpf(sp, -e0), dmin = ldexpf(irho - tauM, e1);
           // Halley's step, at most twice Newton's
-          const float q = sqrtf(g0) / sp - 1.0f;
+          const float q = fminf(sqrtf(g0) / sh - 1.0f, 1e30f);
           float d = 2.f * q * g0 * g1 / fmaxf(g1 * g1, fmaf(3.f * q, fmaf(g1, g1, -g0 * g2), 2.f * g1 * g1));
-          d = fmaxf(d, irho - tauM);
-          const float lam = sqrtf(g6 / g4);   // rate of the series (at most the largest eigenvalue of M)
-          if (fabsf(d) * lam < 0.3f) {
+          d = fmaxf(d, dmin);
+          // rate of the series at its end (at most the largest eigenvalue of M; not
+          // finite if u_3 overflows: then the step has to invert)
+          const float lam = sqrtf(g6 / g4);
+          bool conv = fabsf(d) * lam < 0.3f;
+          if (conv) {
             // Newton on the polynomial N(d)
+            float p = d;
 #pragma unroll 1
             for (int j = 0; j < 3; ++j) {
-              const float e = -d;
+              const float e = -p;
               const float N = fmaf(e, fmaf(e, fmaf(e, fmaf(e, fmaf(e, fmaf(e, 7.f * g6, 6.f * g5), 5.f * g4), 4.f * g3),
                                            3.f * g2), 2.f * g1), g0);
               const float D = fmaf(e, fmaf(e, fmaf(e, fmaf(e, fmaf(e, 42.f * g6, 30.f * g5), 20.f * g4), 12.f * g3),
                                            6.f * g2), 2.f * g1);   // -dN / dd
-              d = fmaxf(fmaf(2.f * N, (sqrtf(N) / sp - 1.0f) / D, d), irho - tauM);
+              p = fmaxf(fmaf(2.f * N, (sqrtf(N) / sh - 1.0f) / D, p), dmin);
             }
+            conv = fabsf(p) * lam < 0.3f;   // (the root is where the polynomial holds)
+            d = conv ? p : d;
           }
           const float d2 = d * d;
-          c32 xn = c32{fmaf(-d, u1.re, u0.re), fmaf(-d, u1.im, u0.im)};
-          xn = c32{fmaf(d2, fmaf(-d, u3.re, u2.re), xn.re), fmaf(d2, fmaf(-d, u3.im, u2.im), xn.im)};
-          const float e = dot(xn, xn);
           // the tail of the series, about d^4 ||u_3|| lam, below half a unit of FP32 rounding
-          const bool last = it >= kBudgetSteps;
-          const bool done = last || d2 * d2 * sqrtf(g6) * lam <= 3e-8f * sp;
+          const bool tail = conv && d2 * d2 * sqrtf(g6) * lam <= 3e-8f * sh;
+          const bool done = tail || it >= kBudgetSteps;
+          c32 xn = u0;   // (out of steps: the solution at the last shift)
+          if (tail) {
+            xn = c32{fmaf(-d, u1.re, u0.re), fmaf(-d, u1.im, u0.im)};
+            xn = c32{fmaf(d2, fmaf(-d, u3.re, u2.re), xn.re), fmaf(d2, fmaf(-d, u3.im, u2.im), xn.im)};
+          }
+          const float e = dot(xn, xn);
           if (need && done) {
             // on the budget up to rounding; a final scale keeps it feasible
-            xa = (e > Pc) ? cscale(xn, sqrtf(Pc / e)) : xn;
+            xa = cldexp(cscale(xn, e > sh * sh ? sh / sqrtf(e) : 1.f), e0);
             need = false;
           }
           if (!__ballot(need)) break;
           // (a problem that is done or below its budget inverts at its old shift again)
-          if (need) tauM += d;
+          if (need) tauM += ldexpf(d, -e1);
           if constexpr (KEEP) {
             const float* st = reinterpret_cast<const float*>(sm.stage + wave * kStageWave) + lane;
             Tile16 T[2];
