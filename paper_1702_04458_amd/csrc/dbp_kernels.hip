@@ -2969,7 +2969,7 @@ constexpr int kBudgetSteps = 12;
 // When the unconstrained step exceeds the budget, x = x(tau) = (H_c^H H_c +
 // tau I)^{-1} H_c^H v with tau > 1/rho the root of ||x(tau)||^2 = P_c (the
 // Lagrange multiplier of the budget is rho tau - 1).  The kernel keeps the
-// inverse M at the shift tau_M of the last inversion (first 1/rho).  For a
+// inverse M at the shift tau_M of the symbol's last inversion (first 1/rho).  For a
 // right-hand side r its powers u_j = M^{j+1} r, j = 0 .. 3, give x at any nearby
 // shift, x(tau_M + d) = sum_j (-d)^j u_j, and through their inner products
 // g_m = r^H M^{m+2} r the squared norm N(d) = sum_m (m + 1) (-d)^m g_m, m <= 6.
@@ -3160,12 +3160,6 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
     }
   }
 
-  c32 Mt[BUDGET ? NR : 1];   // inverse at the shift tauM
-  float tauM = irho;
-  if constexpr (BUDGET) {
-#pragma unroll
-    for (int i = 0; i < NR; ++i) Mt[i] = A[i];
-  }
   if constexpr (KEEP) {
     // the Gram waits in the wave's stage buffer, which is free from here on
     // with the split rows (lane-private slots)
@@ -3187,6 +3181,14 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
     const size_t vo = ((size_t)k * a.n_sym + n);
     const c32 s = (k < a.n_sc) ? a.s[vo * G + u] : cz();
     c32 z = cscale(s, a.f0), lam = cz();
+    // inverse at the shift tauM; every symbol starts from 1/rho (kept from the
+    // symbol before, its result would depend on that symbol)
+    c32 Mt[BUDGET ? NR : 1];
+    float tauM = irho;
+    if constexpr (BUDGET) {
+#pragma unroll
+      for (int i = 0; i < NR; ++i) Mt[i] = A[i];
+    }
     // H_c^H v: entry a held by lane a < S
     auto hhv = [&](c32 v) -> c32 {
       c32 acc = cz();
