@@ -1204,9 +1204,11 @@ __device__ __forceinline__ void tile_sweep_pair(Tile16 (&P)[2], Tile16 (*Q)[2], 
     const float pr[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const float sc = -pc * pr[r], dg = (4 * q + r == col) ? 2.f * pc : 0.f;
-      P[p].re[r] = fmaf(sc, s[8 * p + r], dg);
-      P[p].im[r] = sc * s[8 * p + 4 + r];
+      // (one reciprocal after the other: their product leaves FP32 where the
+      // Gram is below 1e-19 or above 1e19)
+      const float dg = (4 * q + r == col) ? 2.f * pc : 0.f;
+      P[p].re[r] = fmaf(pr[r], -pc * s[8 * p + r], dg);
+      P[p].im[r] = pr[r] * (-pc * s[8 * p + 4 + r]);
       if constexpr (BORDER) {
         (*Q)[p].re[r] = pr[r] * sq[8 * p + r];
         (*Q)[p].im[r] = pr[r] * sq[8 * p + 4 + r];
@@ -1623,9 +1625,10 @@ __device__ __forceinline__ void invert_blocks_u64(f32x16 (&re)[2][2], f32x16 (&i
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int r = 4 * g + t;
-        const float sc = -pc * pr[t], dg = (8 * g + 4 * h + t == col) ? 2.f * pc : 0.f;
-        re[I][I][r] = fmaf(sc, re[I][I][r], dg);
-        im[I][I][r] *= sc;
+        // (one reciprocal after the other, as in tile_sweep_pair)
+        const float dg = (8 * g + 4 * h + t == col) ? 2.f * pc : 0.f;
+        re[I][I][r] = fmaf(pr[t], -pc * re[I][I][r], dg);
+        im[I][I][r] = pr[t] * (-pc * im[I][I][r]);
         if (I == 0) {
           re[0][1][r] *= pr[t];
           im[0][1][r] *= pr[t];
@@ -2684,12 +2687,18 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
       }
     }
     if constexpr (LAZY) {
-      // 2 D - D S D, each entry rounded once (the scales' product as a pair)
+      // 2 D - D S D, each entry rounded once (the scales' product as a pair, of
+      // their mantissas: the powers of two go to the entry, which they bring to
+      // the size of the result)
+      const float ml = __builtin_amdgcn_frexp_mantf(pvl);
+      const int el = __builtin_amdgcn_frexp_expf(pvl);
       static_for<16>([&](auto vc) {
         constexpr int v = decltype(vc)::value;
-        const float pv = bcast16<v>(pvl);
-        const float hi = -pvl * pv, lo = fmaf(-pvl, pv, -hi);
-        A[v] = c32{fmaf(hi, A[v].re, fmaf(lo, A[v].re, u == v ? 2.f * pvl : 0.f)), fmaf(hi, A[v].im, lo * A[v].im)};
+        const float mv = bcast16<v>(ml);
+        const int ev = el + __builtin_amdgcn_mov_dpp(el, 0x150 + v, 0xF, 0xF, true);
+        const float hi = -ml * mv, lo = fmaf(-ml, mv, -hi);
+        const c32 s = cldexp(A[v], ev);
+        A[v] = c32{fmaf(hi, s.re, fmaf(lo, s.re, u == v ? 2.f * pvl : 0.f)), fmaf(hi, s.im, lo * s.im)};
       });
     }
     rows_to_operands<G>(A);
