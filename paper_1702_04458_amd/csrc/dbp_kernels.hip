@@ -3044,7 +3044,7 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
   // every product instead, A_c is formed and inverted on the matrix cores.
   // B = 512, C = 8, S = 64, 1200 subcarriers, T = 5: 8.82 -> 1.29 ms; B = 92,
   // C = 2, S = 46, 1981 subcarriers: 3.01 -> 0.50 ms.
-  constexpr bool STREAM = (G == 64 && SG == 64 && !BUDGET);
+  constexpr bool STREAM = (G == 64 && SG == 64);
   constexpr int kUnroll = STREAM ? 4 : 16;   // (STREAM: 16 loads in flight)
   DlBlock64 hb{};
   if constexpr (STREAM) {
@@ -3103,6 +3103,24 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
       if (v == u) M[v].re += (u < S) ? tau : 1.0f;
     gj_invert<NR>(M, u, line, gbase);
   };
+  // STREAM: Gram and inverse on the matrix cores (tau is the same on every lane)
+  auto stream_invert = [&](c32 (&M)[NR], float tau) {
+    if constexpr (STREAM) {
+      UlArgs ua{};
+      ua.H = a.H;
+      ua.y = a.H;   // (not read)
+      ua.n_sc = a.n_sc;
+      ua.B = a.B;
+      ua.C = a.C;
+      ua.Cp = a.Cp;
+      ua.S = 64;    // rows of H_c: the users
+      ua.sc_per_block = a.sc_per_block;
+      ua.rho = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tau)));
+      ua.blk = blockIdx.x;
+      gram_mfma_u64<2, true>(ua, M, lane, wave, reinterpret_cast<float*>(line),
+                             reinterpret_cast<float*>(sm.stage + wave * kStageWave), &hb);
+    }
+  };
   // the budgeted step inverts the Gram again at other shifts
   constexpr bool KEEP = BUDGET && ASPLIT;
   Tile16 gk[KEEP ? 2 : 1];
@@ -3116,19 +3134,7 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
     // (the vector sweep in both forms: a budget that never binds changes nothing)
     shift_invert_s16<false>(T, irho, irho, S, A, lane, line);
   } else if constexpr (STREAM) {
-    UlArgs ua{};
-    ua.H = a.H;
-    ua.y = a.H;   // (not read)
-    ua.n_sc = a.n_sc;
-    ua.B = a.B;
-    ua.C = a.C;
-    ua.Cp = a.Cp;
-    ua.S = 64;    // rows of H_c: the users
-    ua.sc_per_block = a.sc_per_block;
-    ua.rho = irho;
-    ua.blk = blockIdx.x;
-    gram_mfma_u64<2, true>(ua, A, lane, wave, reinterpret_cast<float*>(line),
-                           reinterpret_cast<float*>(sm.stage + wave * kStageWave), &hb);
+    stream_invert(A, irho);
   } else {
     gram_into(A);
     if constexpr (BUDGET) {
@@ -3341,6 +3347,8 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
             }
             auto tau_of = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tauM), l)); };
             shift_invert_s16<true>(T, tau_of(0), tau_of(32), S, Mt, lane, line);
+          } else if constexpr (STREAM) {
+            stream_invert(Mt, tauM);
           } else {
 #pragma unroll
             for (int i = 0; i < NR; ++i) Mt[i] = cz();
