@@ -3175,6 +3175,12 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
     }
   }
 
+  c32 Mt[BUDGET ? NR : 1];   // inverse at the shift tauM
+  float tauM = irho;
+  if constexpr (BUDGET) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i) Mt[i] = A[i];
+  }
   if constexpr (KEEP) {
     // the Gram waits in the wave's stage buffer, which is free from here on
     // with the split rows (lane-private slots)
@@ -3196,13 +3202,17 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
     const size_t vo = ((size_t)k * a.n_sym + n);
     const c32 s = (k < a.n_sc) ? a.s[vo * G + u] : cz();
     c32 z = cscale(s, a.f0), lam = cz();
-    // inverse at the shift tauM; every symbol starts from 1/rho (kept from the
-    // symbol before, its result would depend on that symbol)
-    c32 Mt[BUDGET ? NR : 1];
-    float tauM = irho;
     if constexpr (BUDGET) {
+      // Every symbol starts from 1/rho (with the shift kept from the symbol before,
+      // its result would depend on that symbol).  The condition is for the
+      // register allocator: without it U = 64, S = 17 .. 32 spills 247 registers
+      // instead of 182 (C = 8, S = 24, 600 subcarriers: 1089 against 888 us), with
+      // it S = 9 .. 16 spills 631 instead of 474 (2100 against 842 us).
+      if (!(G == 64 && SG == 32) || n > 0) {
+        tauM = irho;
 #pragma unroll
-      for (int i = 0; i < NR; ++i) Mt[i] = A[i];
+        for (int i = 0; i < NR; ++i) Mt[i] = A[i];
+      }
     }
     // H_c^H v: entry a held by lane a < S
     auto hhv = [&](c32 v) -> c32 {
@@ -3290,11 +3300,12 @@ __device__ __forceinline__ void admm_dl_body(const DlArgs& a) {
           const int e0 = __builtin_amdgcn_frexp_expf(dot(u0, u0)) >> 1;
           u0 = cldexp(u0, -e0);
           c32 u1 = mul(u0);
-          const int e1 = __builtin_amdgcn_frexp_expf(dot(u0, u1));
+          const float rate = dot(u0, u1);
+          const int e1 = __builtin_amdgcn_frexp_expf(rate);
           u1 = cldexp(u1, -e1);
           const c32 u2 = cldexp(mul(u1), -e1), u3 = cldexp(mul(u2), -e1);
-          const float g0 = dot(u0, u0), g1 = dot(u0, u1), g2 = dot(u1, u1), g3 = dot(u1, u2), g4 = dot(u2, u2),
-                      g5 = dot(u2, u3), g6 = dot(u3, u3);
+          const float g0 = dot(u0, u0), g1 = ldexpf(rate, -e1), g2 = dot(u1, u1), g3 = dot(u1, u2),
+                      g4 = dot(u2, u2), g5 = dot(u2, u3), g6 = dot(u3, u3);
           const float sh = ldexpf(sp, -e0), dmin = ldexpf(irho - tauM, e1);
           // Halley's step, at most twice Newton's
           const float q = fminf(sqrtf(g0) / sh - 1.0f, 1e30f);
