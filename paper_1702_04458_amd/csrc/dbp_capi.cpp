@@ -717,6 +717,7 @@ int dbp_detect_admm_batch(const dbp_frame* frames, int n_frames, int U, void* st
   if (n_frames > 0 && !frames) return fail(DBP_ERR_INVALID, "%s: null frames", who);
   if (!supported_u(U)) return fail(DBP_ERR_UNSUPPORTED, "%s: U=%d not built (8, 16, 32, 64)", who, U);
   // validation of every frame, and the common waves per workgroup
+  // (C_max: over the frames of the FP64 pass, whose slots it sizes)
   int nw = 1, C_max = 1;
   for (int i = 0; i < n_frames; ++i) {
     const dbp_frame& fr = frames[i];
@@ -734,12 +735,13 @@ int dbp_detect_admm_batch(const dbp_frame* frames, int n_frames, int U, void* st
                     "dbp_detect_workspace_bytes bytes", who, i);
     }
     nw = a.nw > nw ? a.nw : nw;
-    C_max = fr.C > C_max ? fr.C : C_max;
+    if (fr.hard && fr.n_sc > 0) C_max = fr.C > C_max ? fr.C : C_max;
   }
   dbp::UlBatch b{};
   dbp::FixBatch fb{};
   fb.slot_c = C_max;
-  // FP64 slots: in the workspace (after its flags) with the most room
+  // FP64 slots: in the workspace (after its flags) with the most room (at least
+  // one slot: the frame of C_max clusters has one of its own)
   const size_t slot = dbp::fix64_slot_bytes(U, C_max);
   char* slots = nullptr;
   size_t slot_room = 0;
