@@ -3566,11 +3566,21 @@ hipError_t launch_admm_ul_mixed(const UlArgs& a, int U, int half, int inv, int n
 }
 
 hipError_t launch_admm_ul_f32_batch(const UlBatch& b, int U, int nw, int grid, hipStream_t st) {
-  if (b.n < 1 || grid == 0) return hipSuccess;
-  const dim3 g((unsigned)grid), blk((unsigned)(64 * nw));
+  if (b.n < 1) return hipSuccess;
   bool syms = false;
   for (int i = 0; i < b.n; ++i) syms = syms || symbol_columns(U, b.f[i].n_sym, b.f[i].C);
-  const auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, blk, smem_bytes(nw), st, b); };
+  // (a launch holds fewer than 2^32 work items: 24 frames of one large channel
+  // can exceed that)
+  const int most = (int)(0xffffffffu / (64u * (unsigned)nw));
+  const auto run = [&](auto kernel) {
+    UlBatch part = b;
+    for (int done = 0; done < grid; done += most) {
+      const int g = grid - done < most ? grid - done : most;
+      hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3((unsigned)(64 * nw)), smem_bytes(nw), st, part);
+      for (int i = 0; i < b.n; ++i) part.first[i] -= most;
+      if (grid - done <= most) break;
+    }
+  };
   switch (U) {
     case 8: run(admm_ul_f32_batch<8, false>); break;
     case 16: syms ? run(admm_ul_f32_batch<16, true>) : run(admm_ul_f32_batch<16, false>); break;

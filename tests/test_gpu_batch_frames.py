@@ -36,3 +36,20 @@ def test_batch_soft_frame_of_more_clusters(U, C_soft, n_soft):
     frame's size only, and its workspace holds one."""
     print(f"[gpu] batch slots U={U} C={C_soft} n_soft={n_soft}", file=sys.stderr, flush=True)
     check([frame(1, U, 1, 1, tiny=True, status=True), frame(n_soft, U, C_soft, 2, hard=False)])
+
+
+def test_batch_of_many_work_items():
+    """24 frames over one channel of 1.4 million subcarriers: more than 2^32 work
+    items, with the boundary between two launches inside a frame.  Every frame is
+    the single call's result."""
+    n_sc, U, C, period = 1_400_000, 8, 9, 1000
+    print(f"[gpu] batch 24 x {n_sc} U={U} C={C}", file=sys.stderr, flush=True)
+    fr = inputs.uplink_frame(inputs.frame_seed(83, U, C), period, U * C, U, 16, 15.0)
+    H = torch.from_numpy(fr.H).cuda().repeat(n_sc // period, 1, 1)
+    y = torch.from_numpy(fr.y).cuda().repeat(n_sc // period, 1, 1)
+    f = dict(H=H, y=y, N0=fr.N0, C=C, T=1, qam=16, hard=False)
+    out = api.detect_batch([f] * 24)
+    want, _ = api.detect(H[:period], y[:period], fr.N0, C, 1.0, 1, qam=16, hard=False)
+    torch.cuda.synchronize()
+    for s, _ in out:
+        assert torch.equal(s.view(-1, period, 1, U), want.expand(n_sc // period, period, 1, U))
