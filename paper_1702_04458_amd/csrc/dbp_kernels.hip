@@ -2445,7 +2445,7 @@ __global__ void __launch_bounds__(512, !SYMS ? 1 : G == 16 ? 4 : G == 32 ? 3 : 2
   UlArgs a = b.f[f];
   a.blk = vb - b.first[f];
   if constexpr (SYMS) {
-    if (symbol_columns(G, a.n_sym, a.C)) return admm_ul_body<G, 0, 0, 0, true>(a);
+    if (symbol_columns(G, a.n_sym, a.B, a.S, a.C)) return admm_ul_body<G, 0, 0, 0, true>(a);
   }
   admm_ul_body<G, 0, 0, 0, false>(a);
 }
@@ -3526,7 +3526,7 @@ template <int G, int HALF, int INV>
 static hipError_t launch_stage(const UlArgs& a, int nw, hipStream_t st, int stage) {
   if (stage == 1) return launch(admm_ul_f32<G, HALF, INV, 1>, a, nw, st);
   if constexpr (INV == 0 && G >= 16) {
-    if (symbol_columns(G, a.n_sym, a.C)) return launch(admm_ul_f32<G, HALF, 0, 0, true>, a, nw, st);
+    if (symbol_columns(G, a.n_sym, a.B, a.S, a.C)) return launch(admm_ul_f32<G, HALF, 0, 0, true>, a, nw, st);
   }
   return launch(admm_ul_f32<G, HALF, INV, 0>, a, nw, st);
 }
@@ -3568,7 +3568,7 @@ hipError_t launch_admm_ul_mixed(const UlArgs& a, int U, int half, int inv, int n
 hipError_t launch_admm_ul_f32_batch(const UlBatch& b, int U, int nw, int grid, hipStream_t st) {
   if (b.n < 1) return hipSuccess;
   bool syms = false;
-  for (int i = 0; i < b.n; ++i) syms = syms || symbol_columns(U, b.f[i].n_sym, b.f[i].C);
+  for (int i = 0; i < b.n; ++i) syms = syms || symbol_columns(U, b.f[i].n_sym, b.f[i].B, b.f[i].S, b.f[i].C);
   // (a launch holds fewer than 2^32 work items: 24 frames of one large channel
   // can exceed that)
   const int most = (int)(0xffffffffu / (64u * (unsigned)nw));
@@ -3593,7 +3593,7 @@ hipError_t launch_admm_ul_f32_batch(const UlBatch& b, int U, int nw, int grid, h
 
 template <int U, int STAGE>
 static hipError_t launch_resident(const UlArgs& a, int nw, hipStream_t st) {
-  if (symbol_columns(U, a.n_sym, a.C)) return launch(admm_ul_f32<U, 0, 0, STAGE, true>, a, nw, st);
+  if (symbol_columns(U, a.n_sym, a.B, a.S, a.C)) return launch(admm_ul_f32<U, 0, 0, STAGE, true>, a, nw, st);
   return launch(admm_ul_f32<U, 0, 0, STAGE>, a, nw, st);
 }
 
@@ -3635,7 +3635,7 @@ hipError_t launch_scan_nonfinite(const float* x, size_t floats_per_sc, int n_sc,
 
 template <int U>
 static hipError_t launch_dcg(const UlArgs& a, int nw, hipStream_t st) {
-  return symbol_columns(U, a.n_sym, a.C) ? launch(dcg_ul_f32<U, true>, a, nw, st) : launch(dcg_ul_f32<U>, a, nw, st);
+  return symbol_columns(U, a.n_sym, a.B, a.S, a.C) ? launch(dcg_ul_f32<U, true>, a, nw, st) : launch(dcg_ul_f32<U>, a, nw, st);
 }
 
 hipError_t launch_dcg_ul_f32(const UlArgs& a, int U, int nw, hipStream_t st) {

@@ -118,9 +118,13 @@ size_t smem_bytes(int nw);
 //   95 284 406 448 486 | 226 217 216 217 361
 //   174 566 759 863 956 | 409 412 422 425 724
 //   150 298 582 654 724 | 269 270 274 276 443
-// The 64 / U problems of a wave must be clusters of one subcarrier.
-__host__ __device__ inline bool symbol_columns(int U, int n_sym, int C) {
-  return U >= 16 && n_sym >= (U == 16 ? 4 : U == 32 ? 5 : 3) && C > 32 / U;
+// The 64 / U problems of a wave must be clusters of one subcarrier, and a cluster's
+// rows of H and eight symbols' receive vectors lie within 2 GiB of its first row and
+// entry (the columns read both with 32-bit byte offsets).
+__host__ __device__ inline bool symbol_columns(int U, int n_sym, int B, int S, int C) {
+  const int64_t most = INT32_MAX;
+  return U >= 16 && n_sym >= (U == 16 ? 4 : U == 32 ? 5 : 3) && C > 32 / U && 8 * (int64_t)S * U <= most &&
+         8 * (7 * (int64_t)B + S) <= most;
 }
 // one launch of grid workgroups (nw waves each; the sum of the frames' blocks) over all frames of b
 hipError_t launch_admm_ul_f32_batch(const UlBatch& b, int U, int nw, int grid, hipStream_t st);
