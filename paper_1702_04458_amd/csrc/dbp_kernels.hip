@@ -77,8 +77,12 @@ size_t smem_bytes(int nw) { return sizeof(c32) * (size_t)nw * (kStageWave + kSta
 
 // One pass over the S rows of H_c (and of y_c for symbol n): accumulates the
 // Gram row A[v] += conj(H[s][u]) H[s][v] when WITH_GRAM, and always
-// hy = sum_s conj(H[s][u]) y[s] (row u of H_c^H y_c).
-template <int G, bool WITH_GRAM>
+// hy = sum_s conj(H[s][u]) y[s] (row u of H_c^H y_c).  BUF (U = 64, the one-shot
+// detection): H through buffer loads, whose range check zeroes the rows past S; with
+// a branch per row, the address registers that three waves per SIMD spill were
+// waited for before every load (against stored factors, two waves, the branches
+// measured up to 8 % faster).
+template <int G, bool WITH_GRAM, bool BUF = false>
 __device__ __forceinline__ c32 cluster_pass(const c32* __restrict__ H, const c32* __restrict__ y, c32 (&A)[G],
                                             int k, int c, int n, int u, int g, int lane, int wave, bool active,
                                             int B, int S, int U, int n_sym, const Smem& sm) {
@@ -90,12 +94,23 @@ __device__ __forceinline__ c32 cluster_pass(const c32* __restrict__ H, const c32
   const c32* yk = y + ((size_t)k * n_sym + n) * B + (size_t)c * S;
   for (int s0 = 0; s0 < S; s0 += R) {
     c32 h[R];
+    if constexpr (BUF) {
+      static_assert(G == 64, "one problem per wave");
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<c32*>(Hk + (size_t)s0 * G), 0, active ? min(R, S - s0) * (G * 8) : 0, kBufferWord3);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int s = s0 + r;
-      h[r] = (active && s < S) ? Hk[(size_t)s * U + u] : cz();
-      if (WITH_GRAM) stage[r * 64 + lane] = h[r];
+      for (int r = 0; r < R; ++r)
+        h[r] = __builtin_bit_cast(c32, __builtin_amdgcn_raw_buffer_load_b64(rs, r * (G * 8) + u * 8, 0, 0));
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int s = s0 + r;
+        h[r] = (active && s < S) ? Hk[(size_t)s * U + u] : cz();
+      }
     }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (WITH_GRAM) stage[r * 64 + lane] = h[r];
     if (u < R) {
       const int s = s0 + u;
       yst[u * 8 + g] = (active && s < S) ? yk[s] : cz();
@@ -1377,9 +1392,53 @@ __device__ __forceinline__ c32 gram_blocks_u32(const UlArgs& a, c32 (&A)[32], in
              scatter_sum(hyp[0][0].im, hyp[0][1].im, hyp[1][0].im, hyp[1][1].im)};
 }
 
-// B^{-1} q from the blocks of gram_blocks_u32, q by entry u = 16 h + (lane % 16)
-// of the problem's 32 lanes.  q_1 (and then t) reaches both rows of 16 lanes by
-// v_permlane16_swap and the multiply-adds by row broadcasts: no LDS.
+// B^{-1} q from the blocks of gram_blocks_u32 (G = 32) or invert_blocks_u64 (G = 64):
+// lane u of the problem's upper half (rows) holds column u of Pi and X^H, of the
+// lower half of W and Si.  q_1 (and then t) reaches all lanes through the
+// problem's part of the broadcast line.
+template <int G>
+__device__ __forceinline__ c32 block_matvec(const c32 (&A)[G], c32 q, c32* line, int gbase, int lane, bool upper) {
+  constexpr int H = G / 2;
+  // sum_v conj(A[v0 + v]) x_v, 16 entries at a time in the order of matvec16c
+  auto mul = [&](int v0, const c32* x) -> c32 {
+    c32 acc = cz();
+#pragma unroll
+    for (int j = 0; j < H; j += 16) {
+      c32 s0 = cz(), s1 = cz();
+#pragma unroll
+      for (int i = 0; i < 16; i += 8) {
+        c32 r[8];
+        lds_read_vec<8>(x + j + i, r);
+#pragma unroll
+        for (int v = 0; v < 8; v += 2) {
+          cmacc(s0, A[v0 + j + i + v], r[v]);
+          cmacc(s1, A[v0 + j + i + v + 1], r[v + 1]);
+        }
+      }
+      acc = j ? cadd(acc, cadd(s0, s1)) : cadd(s0, s1);
+    }
+    return acc;
+  };
+  line[lane] = q;
+  wave_lds_sync();
+  const c32 a = mul(0, line + gbase);         // Pi q_1 | W^H q_1
+  const c32 t = csub(q, a);                   // (lower rows) q_2 - W^H q_1
+  __builtin_amdgcn_wave_barrier();            // (a wave's accesses are in order)
+  line[lane] = t;
+  wave_lds_sync();
+  const c32 b = mul(H, line + gbase + H);     // X t | Si t
+  wave_lds_sync();
+  return upper ? csub(a, b) : b;
+}
+
+// The same at U = 32 by row broadcasts: v_permlane16_swap hands q_1 (and then t) to
+// both rows of 16 lanes, no LDS, the same bits.  A product's latency is shorter, but
+// its multiply-adds take about a third longer than those on LDS operands, so it is
+// taken while a SIMD has one wave or the products are few (line_products).  T = 40,
+// four symbols, S = 32 (us, LDS | row broadcasts): C = 2, 600 subcarriers
+// 126 | 111; C = 5, 4800 subcarriers 840 | 1055; T = 5, one symbol, C = 8, 4800:
+// 145 | 141.  (At U = 64 the row broadcasts were slower throughout: T = 40, C = 8,
+// 600 subcarriers, one symbol 329 us against 292.)
 __device__ __forceinline__ c32 block_matvec_u32(const c32 (&A)[32], c32 q, bool upper) {
   auto dup = [](float v, int row) {
     const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -1562,11 +1621,11 @@ __device__ __forceinline__ void acc_mul(const f32x16& xr, const f32x16& xi, cons
 // product X^H = Si W^H takes 64.  The sweep keeps lazy row and column scales
 // (see gj_invert_mfma_u32) and does not negate the diagonal.  Against the sweep
 // of the whole matrix (six per pivot throughout): 320 instead of 384, half the
-// vector instructions in the second half, products without LDS, and on
-// ill-conditioned clusters a smaller error.
+// vector instructions in the second half, and on ill-conditioned clusters a
+// smaller error.
 // FULL: A receives row u of B^{-1} (one more product, Pi + X W^H).  Otherwise
 // lane u < 32 receives column u of Pi in A[0 .. 31] and of X^H in A[32 .. 63],
-// lane 32 + u column u of W and of Si, for block_matvec_u64.  f2 (may be null):
+// lane 32 + u column u of W and of Si, for block_matvec.  f2 (may be null):
 // ||B^{-1}||_F^2.
 template <bool FULL>
 __device__ __forceinline__ void invert_blocks_u64(f32x16 (&re)[2][2], f32x16 (&im)[2][2], int lane, float rho,
@@ -1671,26 +1730,6 @@ __device__ __forceinline__ void invert_blocks_u64(f32x16 (&re)[2][2], f32x16 (&i
     A[32 + m0] = c32{hr.lo, hi.lo};
     A[32 + m0 + 4] = c32{hr.hi, hi.hi};
   }
-}
-
-// B^{-1} q from the blocks of invert_blocks_u64 (as block_matvec_u32): the two
-// rows of 16 lanes of an operand are handed to all four by three swaps.
-__device__ __forceinline__ c32 block_matvec_u64(const c32 (&A)[64], c32 q, bool upper) {
-  auto spread = [](float v, int half, float& r0, float& r1) {
-    const unsigned u = __float_as_uint(v);
-    const auto e = __builtin_amdgcn_permlane16_swap(u, u, false, false);   // even | odd rows, in pairs
-    r0 = __uint_as_float(__builtin_amdgcn_permlane32_swap(e[0], e[0], false, false)[half]);
-    r1 = __uint_as_float(__builtin_amdgcn_permlane32_swap(e[1], e[1], false, false)[half]);
-  };
-  c32 x0, x1;
-  spread(q.re, 0, x0.re, x1.re);
-  spread(q.im, 0, x0.im, x1.im);
-  const c32 a = cadd(matvec16c<0>(A, x0), matvec16c<16>(A, x1));     // Pi q_1 | W^H q_1
-  const c32 t = csub(q, a);                                          // (upper half of the wave) q_2 - W^H q_1
-  spread(t.re, 1, x0.re, x1.re);
-  spread(t.im, 1, x0.im, x1.im);
-  const c32 b = cadd(matvec16c<32>(A, x0), matvec16c<48>(A, x1));    // X t | Si t
-  return upper ? csub(a, b) : b;
 }
 
 // accumulator tiles -> lane-row layout: lane u < 32 takes column u of tile
@@ -2418,13 +2457,17 @@ __device__ __forceinline__ int syms_iterate(const UlArgs& a, const c32 (&A)[G], 
 // read from a.fac (every symbol's H_c^H y_c by the VALU pass); 3 as 2 with H
 // read from the packed FP16 channel; 4 (U = 32, FP32) as 1, and H also
 // written as the packed FP16 channel in the same launch.
-template <int G, int HALF, int INV, int STAGE, bool SYMS>
+// LINE: the block factors' products at U = 32 through the broadcast line
+// (block_matvec) instead of row broadcasts (block_matvec_u32).
+template <int G, int HALF, int INV, int STAGE, bool SYMS, bool LINE>
 __device__ __forceinline__ void admm_ul_body(const UlArgs& a);
 
-template <int G, int HALF, int INV, int STAGE, bool SYMS = false>
-__global__ void __launch_bounds__(512, !SYMS ? 1 : G == 16 ? 4 : G == 32 ? 3 : 2) admm_ul_f32(UlArgs a) {
+// Registers: at U = 64 three waves per SIMD (168; two with 171: C = 3, T = 40, 600
+// subcarriers 155 us against 123).
+template <int G, int HALF, int INV, int STAGE, bool SYMS = false, bool LINE = false>
+__global__ void __launch_bounds__(512, !SYMS ? (G == 64 && HALF == 0 && STAGE == 0 ? 3 : LINE ? 4 : 1) : G == 16 ? 4 : G == 32 ? 3 : 2) admm_ul_f32(UlArgs a) {
   a.blk = blockIdx.x;
-  admm_ul_body<G, HALF, INV, STAGE, SYMS>(a);
+  admm_ul_body<G, HALF, INV, STAGE, SYMS, LINE>(a);
 }
 
 // Several frames of the same U in one launch (FP32, one-shot): frame f owns the
@@ -2435,9 +2478,13 @@ __global__ void __launch_bounds__(512, !SYMS ? 1 : G == 16 ? 4 : G == 32 ? 3 : 2
 // arguments.  One block of subcarriers per workgroup: with a persistent grid
 // (1024 workgroups in a loop over the blocks) eight uneven U = 16 frames took
 // 57 us instead of 55, the loop's registers costing a wave per SIMD.
-// SYMS: some frame takes the column form of the iterations (symbol_columns).
-template <int G, bool SYMS>
-__global__ void __launch_bounds__(512, !SYMS ? 1 : G == 16 ? 4 : G == 32 ? 3 : 2) admm_ul_f32_batch(UlBatch b) {
+// SYMS: some frame takes the column form of the iterations (symbol_columns).  One
+// launch for both forms, though the columns' registers cost the other frames a wave
+// per SIMD: eight frames, one of them of seven symbols (us, one launch | one per
+// form): U = 16, 12 subcarriers each 38 | 44, 1200 each 90 | 98; U = 32, 100 each
+// 50 | 63, 1200 each 356 | 340; U = 64, 12 each 82 | 135, 300 each 556 | 635.
+template <int G, bool SYMS, bool LINE = false>
+__global__ void __launch_bounds__(512, !SYMS ? (G == 64 ? 3 : LINE ? 4 : 1) : G == 16 ? 4 : G == 32 ? 3 : 2) admm_ul_f32_batch(UlBatch b) {
   const int vb = blockIdx.x;
   int f = 0;
 #pragma unroll
@@ -2445,12 +2492,12 @@ __global__ void __launch_bounds__(512, !SYMS ? 1 : G == 16 ? 4 : G == 32 ? 3 : 2
   UlArgs a = b.f[f];
   a.blk = vb - b.first[f];
   if constexpr (SYMS) {
-    if (symbol_columns(G, a.n_sym, a.B, a.S, a.C)) return admm_ul_body<G, 0, 0, 0, true>(a);
+    if (symbol_columns(G, a.n_sym, a.B, a.S, a.C, a.T)) return admm_ul_body<G, 0, 0, 0, true, false>(a);
   }
-  admm_ul_body<G, 0, 0, 0, false>(a);
+  admm_ul_body<G, 0, 0, 0, false, LINE>(a);
 }
 
-template <int G, int HALF, int INV, int STAGE, bool SYMS>
+template <int G, int HALF, int INV, int STAGE, bool SYMS, bool LINE>
 __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
   constexpr int P = 64 / G;
   constexpr bool RESIDENT = (STAGE == 2 || STAGE == 3);   // iterations against stored factors
@@ -2495,9 +2542,10 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
       const float tp = 2.f * pvl;
       return c32{fmaf(tp, q.re, -pvl * r.re), fmaf(tp, q.im, -pvl * r.im)};
     } else if constexpr (BLOCKS) {
-      return block_matvec_u32(A, q, (lane & 16) == 0);
+      if constexpr (LINE) return block_matvec<G>(A, q, line, gbase, lane, (lane & 16) == 0);
+      else return block_matvec_u32(A, q, (lane & 16) == 0);
     } else if constexpr (BLOCKS64) {
-      return block_matvec_u64(A, q, lane < 32);
+      return block_matvec<G>(A, q, line, gbase, lane, lane < 32);
     } else {
       return group_matvec<G>(A, q, u, line, gbase);
     }
@@ -2716,7 +2764,8 @@ __device__ __forceinline__ void admm_ul_body(const UlArgs& a) {
     if constexpr (STAGE == 3) {
       if (!HY0 || n > 0) hy = cluster_hy_direct<G, true>(a, k, c, n, u, active);
     } else if (n > 0 || (STAGE == 2 && !HY0)) {
-      hy = cluster_pass<G, false>(a.H, a.y, A, k, c, n, u, g, lane, wave, active, a.B, a.S, G, a.n_sym, sm);
+      hy = cluster_pass<G, false, G == 64 && STAGE == 0>(a.H, a.y, A, k, c, n, u, g, lane, wave, active, a.B, a.S, G,
+                                                         a.n_sym, sm);
     }
     // y_c^reg = B_c^{-1} H_c^H y_c; z = y^reg; lambda = 0
     const c32 yreg = bmat(hy);
@@ -3522,11 +3571,22 @@ static hipError_t launch(K kernel, const Args& a, int nw, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Products of the block factors at U = 32 through LDS (see block_matvec_u32; the same
+// bits either way): more than one wave per SIMD (256 CUs of four) and 16 products or
+// more.
+static bool line_products(long blocks, int nw, int n_sym, int T) {
+  return (blocks + 255) / 256 * nw > 4 && (long)n_sym * T >= 16;
+}
+
 template <int G, int HALF, int INV>
 static hipError_t launch_stage(const UlArgs& a, int nw, hipStream_t st, int stage) {
   if (stage == 1) return launch(admm_ul_f32<G, HALF, INV, 1>, a, nw, st);
   if constexpr (INV == 0 && G >= 16) {
-    if (symbol_columns(G, a.n_sym, a.B, a.S, a.C)) return launch(admm_ul_f32<G, HALF, 0, 0, true>, a, nw, st);
+    if (symbol_columns(G, a.n_sym, a.B, a.S, a.C, a.T)) return launch(admm_ul_f32<G, HALF, 0, 0, true>, a, nw, st);
+  }
+  if constexpr (G == 32 && HALF == 0) {
+    if (line_products((a.n_sc + a.sc_per_block - 1) / a.sc_per_block, nw, a.n_sym, a.T))
+      return launch(admm_ul_f32<32, 0, 0, 0, false, true>, a, nw, st);
   }
   return launch(admm_ul_f32<G, HALF, INV, 0>, a, nw, st);
 }
@@ -3567,8 +3627,9 @@ hipError_t launch_admm_ul_mixed(const UlArgs& a, int U, int half, int inv, int n
 
 hipError_t launch_admm_ul_f32_batch(const UlBatch& b, int U, int nw, int grid, hipStream_t st) {
   if (b.n < 1) return hipSuccess;
-  bool syms = false;
-  for (int i = 0; i < b.n; ++i) syms = syms || symbol_columns(U, b.f[i].n_sym, b.f[i].B, b.f[i].S, b.f[i].C);
+  bool syms = false, line = false;
+  for (int i = 0; i < b.n; ++i) line = line || line_products(grid, nw, b.f[i].n_sym, b.f[i].T);
+  for (int i = 0; i < b.n; ++i) syms = syms || symbol_columns(U, b.f[i].n_sym, b.f[i].B, b.f[i].S, b.f[i].C, b.f[i].T);
   // (a launch holds fewer than 2^32 work items: 24 frames of one large channel
   // can exceed that)
   const int most = (int)(0xffffffffu / (64u * (unsigned)nw));
@@ -3584,7 +3645,11 @@ hipError_t launch_admm_ul_f32_batch(const UlBatch& b, int U, int nw, int grid, h
   switch (U) {
     case 8: run(admm_ul_f32_batch<8, false>); break;
     case 16: syms ? run(admm_ul_f32_batch<16, true>) : run(admm_ul_f32_batch<16, false>); break;
-    case 32: syms ? run(admm_ul_f32_batch<32, true>) : run(admm_ul_f32_batch<32, false>); break;
+    case 32:
+      syms   ? run(admm_ul_f32_batch<32, true, true>)
+      : line ? run(admm_ul_f32_batch<32, false, true>)
+             : run(admm_ul_f32_batch<32, false>);
+      break;
     case 64: syms ? run(admm_ul_f32_batch<64, true>) : run(admm_ul_f32_batch<64, false>); break;
     default: return hipErrorInvalidValue;
   }

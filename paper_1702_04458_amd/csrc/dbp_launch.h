@@ -102,28 +102,34 @@ size_t smem_bytes(int nw);
 // Whether a detection call takes its symbols as matrix columns, eight at a time
 // (syms_iterate).  The columns cost the same for one symbol as for eight, the
 // vector form a constant per symbol; measured per call with 1, the line's number,
-// 7, 8 and 9 symbols (vector | columns, us):
-//   U = 16 (19200 subcarriers, B = 128, C = 8)  142 290 393 429 474 | 291 271 267 270 431   from 4
-//   U = 32 (9536 subcarriers, B = 256, C = 8)   272 609 783 867 946 | 540 543 544 549 845   from 5
-//   U = 64 (1192 subcarriers, B = 512, C = 8)   259 413 712 788 861 | 396 398 403 403 577   from 3
+// 7, 8 and 9 symbols (vector | columns, us; T = 5):
+//   U = 16 (19200 subcarriers, B = 128, C = 8)  149 271 399 434 485 | 290 265 273 267 431   from 4
+//   U = 32 (9536 subcarriers, B = 256, C = 8)   271 635 793 873 957 | 538 542 546 543 841   from 5
+//   U = 64 (1192 subcarriers, B = 512, C = 8)   256 419 741 819 898 | 394 396 398 399 574   from 3
 // Against stored factors, same sizes (1, the line's number, 7, 8, 9; complex64 H,
 // the packed channel's figures are within 15 %):
-//   84 227 349 394 428 | 186 188 193 197 354
-//   168 514 687 770 861 | 358 367 370 372 662
-//   173 317 597 668 737 | 247 251 255 256 422
+//   85 208 336 374 418 | 186 188 193 194 355
+//   169 515 681 773 851 | 361 367 372 376 671
+//   172 316 596 669 736 | 250 252 257 259 426
 // and with the split FP16 Gram, U = 32 and 64:
-//   473 738 894 987 1081 | 659 607 612 611 881
-//   298 443 731 807 877 | 420 423 429 429 598
+//   376 697 879 977 1057 | 591 593 596 597 876
+//   262 396 648 711 772 | 393 396 396 400 568
 // and by conjugate gradients:
-//   95 284 406 448 486 | 226 217 216 217 361
-//   174 566 759 863 956 | 409 412 422 425 724
-//   150 298 582 654 724 | 269 270 274 276 443
+//   90 248 369 432 467 | 200 202 204 204 357
+//   180 554 727 811 901 | 407 411 411 414 722
+//   139 291 578 648 721 | 268 270 273 274 444
+// On the line itself the two are close.  Columns over vector at the line's number,
+// 16 to 4800 subcarriers, S = U and 4 U, C = 1 to 16, T = 1 to 20: U = 16 0.38 to
+// 1.04, U = 32 0.28 to 1.01; U = 64, T <= 5, 0.31 to 1.01, with three clusters in
+// one shot up to 1.17 (their workgroups of four waves fill the chip unevenly); U =
+// 64, T = 20, up to 1.36 in one shot, where the line moves to four (0.58 to 1.12
+// there), and up to 1.13 in the other forms, which keep it (T = 0 stands for them).
 // The 64 / U problems of a wave must be clusters of one subcarrier, and a cluster's
 // rows of H and eight symbols' receive vectors lie within 2 GiB of its first row and
 // entry (the columns read both with 32-bit byte offsets).
-__host__ __device__ inline bool symbol_columns(int U, int n_sym, int B, int S, int C) {
+__host__ __device__ inline bool symbol_columns(int U, int n_sym, int B, int S, int C, int T = 0) {
   const int64_t most = INT32_MAX;
-  return U >= 16 && n_sym >= (U == 16 ? 4 : U == 32 ? 5 : 3) && C > 32 / U && 8 * (int64_t)S * U <= most &&
+  return U >= 16 && n_sym >= (U == 16 ? 4 : U == 32 ? 5 : T > 8 && C > 1 ? 4 : 3) && C > 32 / U && 8 * (int64_t)S * U <= most &&
          8 * (7 * (int64_t)B + S) <= most;
 }
 // one launch of grid workgroups (nw waves each; the sum of the frames' blocks) over all frames of b

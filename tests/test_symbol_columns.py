@@ -12,7 +12,7 @@ HIP = "/opt/rocm/include/hip/hip_runtime.h"
 
 pytestmark = pytest.mark.skipif(not (shutil.which("g++") and os.path.exists(HIP)), reason="no g++ or HIP headers")
 
-CASES = [  # U, n_sym, B, C, columns
+CASES = [  # U, n_sym, B, C, columns (T <= 8)
     (8, 14, 64, 8, False),
     (16, 3, 128, 8, False), (16, 4, 128, 8, True), (16, 4, 32, 2, False), (16, 4, 48, 3, True),
     (32, 4, 256, 8, False), (32, 5, 256, 8, True), (32, 5, 32, 1, False), (32, 5, 64, 2, True),
@@ -23,12 +23,15 @@ CASES = [  # U, n_sym, B, C, columns
     (64, 3, 4_194_303, 1, True), (64, 3, 4_194_304, 1, False), (32, 5, 2 * 8_388_608, 2, False),
 ]
 
+MANY = [(64, 3, 512, 8, False), (64, 4, 512, 8, True), (64, 3, 64, 1, True), (16, 4, 128, 8, True)]   # T = 9
+
 
 def test_symbol_columns_rule(tmp_path):
     src, exe = tmp_path / "rule.cpp", tmp_path / "rule"
-    calls = "".join(f'  putchar(dbp::symbol_columns({u}, {n}, {b}, {b // c}, {c}) ? \'1\' : \'0\');\n' for u, n, b, c, _ in CASES)
+    calls = "".join(f"  putchar(dbp::symbol_columns({u}, {n}, {b}, {b // c}, {c}, {t}) ? '1' : '0');\n"
+                    for t, cases in ((8, CASES), (9, MANY)) for u, n, b, c, _ in cases)
     src.write_text('#include <cstdio>\n#include "dbp_launch.h"\nint main() {\n' + calls + "}\n")
     subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                     "-I" + os.path.join(ROOT, "paper_1702_04458_amd", "csrc"), str(src), "-o", str(exe)], check=True)
     got = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout
-    assert got == "".join("1" if want else "0" for *_, want in CASES)
+    assert got == "".join("1" if want else "0" for *_, want in CASES + MANY)
