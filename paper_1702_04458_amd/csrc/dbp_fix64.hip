@@ -125,8 +125,11 @@ struct FixList {
 // window is `wt` chunks from chunk0 on, one per wave (wt is at most the waves
 // of the workgroup).  Every workgroup ranks the flagged subcarriers of the
 // window in index order and takes those of rank q0, q0 + G, ... into
-// list[0 .. n), which must fit kListCap; returns n, and the number of flagged
-// subcarriers of the window in *total.
+// list[0 .. n), which must fit kListCap, with (G, q0) = share(number of flagged
+// subcarriers of the window); returns n, and that number in *total.
+struct Share {
+  int G, q0;
+};
 // (wt so that a workgroup's share, at most wt kChunk / G, fits the list)
 __device__ __forceinline__ int fix_window(int waves, int G) { return waves < G ? waves : G; }
 __device__ __forceinline__ long frame_chunks(const FixArgs& f) { return ((long)f.n_sc + kChunk - 1) / kChunk; }
@@ -138,9 +141,9 @@ __device__ __forceinline__ long fix_chunks(const FR& fr, unsigned act) {
   return c;
 }
 
-template <class FR>
-__device__ __forceinline__ int collect_window(const FR& fr, unsigned act, long chunk0, int wt, int G, int q0, FixList& L,
-                                              int* total_out) {
+template <class FR, class F>
+__device__ __forceinline__ int collect_window(const FR& fr, unsigned act, long chunk0, int wt, FixList& L, int* total_out,
+                                              F share) {
   __syncthreads();   // the previous round's list and sums are no longer read
   const int lane = threadIdx.x & 63, nwv = blockDim.x >> 6;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -163,20 +166,25 @@ __device__ __forceinline__ int collect_window(const FR& fr, unsigned act, long c
   unsigned bits = 0;   // bit i: flag base + 64 i + lane
   int mine = 0;        // flagged subcarriers of the chunk
   if (flags) {
+    // (no branches and no masks kept per flag: a lane past the end reads the last
+    // flag again and drops it from its bits)
+    const int room = (int)(end - base < kChunk ? end - base : kChunk);   // >= 1
+    int l = lane;
+    asm volatile("" : "+v"(l));   // (or the 32 offsets are kept over the windows)
     int v[kScan];
 #pragma unroll
     for (int i = 0; i < kScan; ++i) {
-      // (no branches: a lane past the end reads the last flag and drops it)
-      const long k = base + 64 * i + lane;
-      v[i] = flags[k < end ? k : end - 1];
-      v[i] = k < end ? v[i] : 0;
+      const int k = 64 * i + l;
+      v[i] = flags[base + (k < room ? k : room - 1)];
     }
 #pragma unroll
-    for (int i = 0; i < kScan; ++i) {
-      const bool on = (v[i] & kStatusReslice) != 0;
-      bits |= on ? 1u << i : 0u;
-      mine += __popcll(__ballot(on));
-    }
+    for (int i = 0; i < kScan; ++i) bits |= (v[i] & kStatusReslice) ? 1u << i : 0u;
+    const int left = room - lane;          // this lane's flags are those of 64 i < left
+    const int valid = left > 0 ? (left + 63) / 64 : 0;
+    bits &= valid >= kScan ? ~0u : (1u << valid) - 1u;
+    const int own = __popc(bits);          // 0 .. 32
+#pragma unroll
+    for (int p = 0; p < 6; ++p) mine += __popcll(__ballot((own >> p) & 1)) << p;
   }
   if (lane == 0) L.wsum[wv] = mine;
   __syncthreads();
@@ -186,7 +194,12 @@ __device__ __forceinline__ int collect_window(const FR& fr, unsigned act, long c
     q += w < wv ? c : 0;
     total += c;
   }
+  const Share sh = share(total);
+  const int G = sh.G, q0 = sh.q0;
   if (mine > 0) {   // wave-uniform
+    // (rolled: 32 copies with their divisions are 10 KB of code, fetched anew by
+    // every launch)
+#pragma unroll 1
     for (int i = 0; i < kScan; ++i) {
       const bool on = (bits >> i) & 1u;
       const unsigned long long m = __ballot(on);
@@ -214,7 +227,7 @@ __device__ __forceinline__ void for_flagged(const FR& fr, unsigned act, int G, i
   for (long c0 = 0; c0 < chunks; c0 += wt) {
     const int q0 = (int)(((long)g - seen % G + G) % G);
     int total = 0;
-    const int nl = collect_window(fr, act, c0, wt, G, q0, L, &total);
+    const int nl = collect_window(fr, act, c0, wt, L, &total, [&](int) { return Share{G, q0}; });
     for (int q = 0; q < nl; ++q)
       if (seen + q0 + (long)q * G >= from)
         body(fr.at(__builtin_amdgcn_readfirstlane((int)L.fr[q])), __builtin_amdgcn_readfirstlane(L.k[q]));
@@ -763,7 +776,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) a
     constexpr int kNone = 1 << 30;
     const long want = (long)g - seen;   // >= 0: the loop ends once it is found
     int total = 0;
-    const int nl = collect_window(fr, 1u, c0, wt, kNone, counting || want > kNone ? kNone : (int)want, list, &total);
+    const int nl = collect_window(fr, 1u, c0, wt, list, &total,
+                                  [&](int) { return Share{kNone, counting || want > kNone ? kNone : (int)want}; });
     if (nl > 0) k = list.k[0];
     seen += total;
     if (counting ? seen > G : k >= 0) break;   // uniform
@@ -854,6 +868,7 @@ __global__ void __launch_bounds__(kFixThreads) dcg_ul_fix64(FixArgs f) {
     for (int e = tid; e < CU; e += kFixThreads) {
       const int c = e / U, i = e - c * U;
       d2 acc = dzero();
+#pragma unroll 4
       for (int s = 0; s < S; ++s) {
         const int j = c * S + s;
         dmacc(acc, dld(rows + (size_t)j * U + i), yv ? dld(yv + j) : Hp[j]);
@@ -872,12 +887,13 @@ __global__ void __launch_bounds__(kFixThreads) dcg_ul_fix64(FixArgs f) {
     __syncthreads();
   };
 
-  // The symbols of a subcarrier are shared by `split` workgroups (nothing but
-  // the load of H[k] is repeated).
-  const int split = f.n_sym < (int)gridDim.x ? (f.n_sym < 16 ? f.n_sym : 16) : 1;
-  const int G = gridDim.x / split, g = blockIdx.x / split, n0 = blockIdx.x % split;
-  if (g >= G) return;   // uniform
-  for_flagged(OneFrame{f}, 1u, G, g, 0, list, [&](const FixArgs&, int k) {
+  // While workgroups outnumber a window's flagged subcarriers, `split` of them
+  // share the symbols of one (nothing but the load of H[k] is repeated): without,
+  // one subcarrier of 17 symbols takes 17 times as long as one of one; with a fixed
+  // split 700 flagged subcarriers of three symbols (U = 16, S = 48) took 486 us
+  // instead of 423.
+  int split = 1, n0 = 0;
+  auto recompute = [&](int k) {
     const c32* Hk = f.H + (size_t)k * B * U;
     if (staged) {
       for (int e = tid; e < B * U; e += kFixThreads) Hs[e] = Hk[e];
@@ -900,6 +916,7 @@ __global__ void __launch_bounds__(kFixThreads) dcg_ul_fix64(FixArgs f) {
         if (B <= kChunk) {
           for (int j = tid; j < B; j += kFixThreads) {
             d2 acc = dzero();
+#pragma unroll 4
             for (int u = 0; u < U; ++u) dmac(acc, dld(rows + (size_t)j * U + u), P[u]);
             Hp[j] = acc;
           }
@@ -914,12 +931,14 @@ __global__ void __launch_bounds__(kFixThreads) dcg_ul_fix64(FixArgs f) {
               for (int s = tid; s < ns; s += kFixThreads) {
                 const c32* row = rows + ((size_t)c * S + s0 + s) * U;
                 d2 acc = dzero();
+#pragma unroll 4
                 for (int u = 0; u < U; ++u) dmac(acc, dld(row + u), P[u]);
                 Hp[s] = acc;
               }
               __syncthreads();
               for (int i = tid; i < U; i += kFixThreads) {
                 d2 acc = dzero();
+#pragma unroll 4
                 for (int s = 0; s < ns; ++s) dmacc(acc, dld(rows + ((size_t)c * S + s0 + s) * U + i), Hp[s]);
                 W[i].re += acc.re;
                 W[i].im += acc.im;
@@ -949,7 +968,24 @@ __global__ void __launch_bounds__(kFixThreads) dcg_ul_fix64(FixArgs f) {
       for (int i = tid; i < U; i += kFixThreads) write_out(f, k, n, i, X[i]);
       __syncthreads();
     }
-  });
+  };
+  const OneFrame fr{f};
+  const int grid = gridDim.x, wt = fix_window(blockDim.x >> 6, grid);
+  const long chunks = fix_chunks(fr, 1u);
+  long seen = 0;
+  for (long c0 = 0; c0 < chunks; c0 += wt) {
+    int total = 0, G = grid, q0 = 0;
+    const int nl = collect_window(fr, 1u, c0, wt, list, &total, [&](int flagged) {
+      split = min(min(f.n_sym, 16), max(1, grid / max(1, flagged)));
+      G = grid / split;
+      const int g = blockIdx.x / split;
+      n0 = blockIdx.x % split;
+      q0 = g < G ? (int)(((long)g - seen % G + G) % G) : flagged;   // (a remainder of the grid: nothing)
+      return Share{G, q0};
+    });
+    for (int q = 0; q < nl; ++q) recompute(__builtin_amdgcn_readfirstlane(list.k[q]));
+    seen += total;
+  }
 }
 
 size_t fix64_slot_bytes(int U, int C) { return (size_t)C * U * U * sizeof(d2); }
