@@ -290,12 +290,12 @@ __device__ __forceinline__ void team_sync() {
 
 // B_c = H_c^H H_c + rho I on the FP64 matrix cores (K runs over four antenna
 // rows: lane l supplies H[s0 + l / 16][16 b + l % 16]), and entries 16 b + tj
-// of H_c^H y_c when HY (the same for every ti).  The loads of the next 16 rows
+// of H_c^H y_c when HY (the same for every ti).  The loads of the next 4 D rows
 // are in flight while the current ones are multiplied.
-template <int U, bool HY>
+template <int U, bool HY, int D = 4>
 __device__ __forceinline__ void team_gram(const c32* __restrict__ Hc, const c32* __restrict__ yc, int S, double rho,
                                           int tw, int lane, Tiles<U>& M, d2 (&hy)[Team<U>::NB]) {
-  constexpr int NB = Team<U>::NB, NI = Team<U>::NI, D = 4;
+  constexpr int NB = Team<U>::NB, NI = Team<U>::NI;
   const int ti = lane >> 4, tj = lane & 15;
   auto& re = M.re;
   auto& im = M.im;
@@ -680,7 +680,9 @@ __device__ __forceinline__ void fix64_subcarrier(const FixArgs& f, int k, d2* ld
   RegInverse<U> inv;
   d2 hy[Team<U>::NB];
   if (c < f.C) {
-    team_gram<U, true>(f.H + (size_t)k * f.B * U + (size_t)c * f.S * U,
+    // (16 waves leave 128 registers: with four groups of rows in flight 190 spilled,
+    // with two 96; B = 1536, U = 32, C = 16, 16 flagged subcarriers 158 -> 145 us)
+    team_gram<U, true, (U == 32 && NW == 16) ? 2 : 4>(f.H + (size_t)k * f.B * U + (size_t)c * f.S * U,
                        f.y + (size_t)k * f.n_sym * f.B + (size_t)c * f.S, f.S, f.rho, 0, lane, inv.M, hy);
     team_invert<U>(inv.M, 0, lane, lds + c * Team<U>::kLds);
   }
