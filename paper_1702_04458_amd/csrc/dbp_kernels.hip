@@ -3563,12 +3563,42 @@ __global__ void __launch_bounds__(256) scan_nonfinite(const float* __restrict__ 
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-template <typename K, typename Args>
-static hipError_t launch(K kernel, const Args& a, int nw, hipStream_t st) {
-  const int nblocks = (a.n_sc + a.sc_per_block - 1) / a.sc_per_block;
-  if (nblocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(64 * nw), smem_bytes(nw), st, a);
-  return hipGetLastError();
+// A launch holds fewer than 2^32 work items (the runtime cuts a larger one off
+// without an error): workgroups of `threads` per launch.
+static long most_blocks(int threads) { return 0xffffffffu / (unsigned)threads; }
+
+// The same call without its first k subcarriers.
+template <int U>
+static void skip(UlArgs& a, size_t k) {
+  a.n_sc -= (int)k;
+  if (a.H) a.H += k * a.B * U;
+  a.y += k * a.n_sym * a.B;
+  if (a.shat) a.shat += k * a.n_sym * U;
+  if (a.hard) a.hard += k * a.n_sym * U;
+  if (a.fac) a.fac += k * a.C * (U * (U + 1) / 2);
+  if (a.H16) a.H16 += k * a.B * U;
+  if (a.hscale) a.hscale += k * a.C;
+  if (a.flags) a.flags += k;
+}
+template <int U>
+static void skip(DlArgs& a, size_t k) {
+  a.n_sc -= (int)k;
+  a.H += k * a.B * U;
+  a.s += k * a.n_sym * U;
+  a.x += k * a.n_sym * a.B;
+  if (a.beta) a.beta += k * a.n_sym;
+}
+
+template <int U, typename K, typename Args>
+static hipError_t launch(K kernel, Args a, int nw, hipStream_t st) {
+  for (;;) {
+    const long blocks = ((long)a.n_sc + a.sc_per_block - 1) / a.sc_per_block, most = most_blocks(64 * nw);
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks < most ? blocks : most)), dim3(64 * nw), smem_bytes(nw), st, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || blocks <= most) return e;
+    skip<U>(a, (size_t)most * a.sc_per_block);
+  }
 }
 
 // Products of the block factors at U = 32 through LDS (see block_matvec_u32; the same
@@ -3580,19 +3610,19 @@ static bool line_products(long blocks, int nw, int n_sym, int T) {
 
 template <int G, int HALF, int INV>
 static hipError_t launch_stage(const UlArgs& a, int nw, hipStream_t st, int stage) {
-  if (stage == 1) return launch(admm_ul_f32<G, HALF, INV, 1>, a, nw, st);
+  if (stage == 1) return launch<G>(admm_ul_f32<G, HALF, INV, 1>, a, nw, st);
   if constexpr (INV == 0 && G >= 16) {
-    if (symbol_columns(G, a.n_sym, a.B, a.S, a.C, a.T)) return launch(admm_ul_f32<G, HALF, 0, 0, true>, a, nw, st);
+    if (symbol_columns(G, a.n_sym, a.B, a.S, a.C, a.T)) return launch<G>(admm_ul_f32<G, HALF, 0, 0, true>, a, nw, st);
   }
   if constexpr (G == 32 && HALF == 0) {
     if (line_products((a.n_sc + a.sc_per_block - 1) / a.sc_per_block, nw, a.n_sym, a.T))
-      return launch(admm_ul_f32<32, 0, 0, 0, false, true>, a, nw, st);
+      return launch<32>(admm_ul_f32<32, 0, 0, 0, false, true>, a, nw, st);
   }
-  return launch(admm_ul_f32<G, HALF, INV, 0>, a, nw, st);
+  return launch<G>(admm_ul_f32<G, HALF, INV, 0>, a, nw, st);
 }
 
 hipError_t launch_factor_pack_u32(const UlArgs& a, int nw, hipStream_t st) {
-  return launch(admm_ul_f32<32, 0, 0, 4>, a, nw, st);
+  return launch<32>(admm_ul_f32<32, 0, 0, 4>, a, nw, st);
 }
 
 hipError_t launch_admm_ul_f32(const UlArgs& a, int U, int nw, hipStream_t st, int stage) {
@@ -3630,9 +3660,8 @@ hipError_t launch_admm_ul_f32_batch(const UlBatch& b, int U, int nw, int grid, h
   bool syms = false, line = false;
   for (int i = 0; i < b.n; ++i) line = line || line_products(grid, nw, b.f[i].n_sym, b.f[i].T);
   for (int i = 0; i < b.n; ++i) syms = syms || symbol_columns(U, b.f[i].n_sym, b.f[i].B, b.f[i].S, b.f[i].C, b.f[i].T);
-  // (a launch holds fewer than 2^32 work items: 24 frames of one large channel
-  // can exceed that)
-  const int most = (int)(0xffffffffu / (64u * (unsigned)nw));
+  // (24 frames of one large channel can exceed a launch)
+  const int most = (int)most_blocks(64 * nw);
   const auto run = [&](auto kernel) {
     UlBatch part = b;
     for (int done = 0; done < grid; done += most) {
@@ -3658,13 +3687,13 @@ hipError_t launch_admm_ul_f32_batch(const UlBatch& b, int U, int nw, int grid, h
 
 template <int U, int STAGE>
 static hipError_t launch_resident(const UlArgs& a, int nw, hipStream_t st) {
-  if (symbol_columns(U, a.n_sym, a.B, a.S, a.C)) return launch(admm_ul_f32<U, 0, 0, STAGE, true>, a, nw, st);
-  return launch(admm_ul_f32<U, 0, 0, STAGE>, a, nw, st);
+  if (symbol_columns(U, a.n_sym, a.B, a.S, a.C)) return launch<U>(admm_ul_f32<U, 0, 0, STAGE, true>, a, nw, st);
+  return launch<U>(admm_ul_f32<U, 0, 0, STAGE>, a, nw, st);
 }
 
 hipError_t launch_admm_ul_factored(const UlArgs& a, int U, int nw, hipStream_t st) {
   switch (U) {
-    case 8: return launch(admm_ul_f32<8, 0, 0, 2>, a, nw, st);
+    case 8: return launch<8>(admm_ul_f32<8, 0, 0, 2>, a, nw, st);
     case 16: return launch_resident<16, 2>(a, nw, st);
     case 32: return launch_resident<32, 2>(a, nw, st);
     case 64: return launch_resident<64, 2>(a, nw, st);
@@ -3674,7 +3703,7 @@ hipError_t launch_admm_ul_factored(const UlArgs& a, int U, int nw, hipStream_t s
 
 hipError_t launch_admm_ul_factored_h16(const UlArgs& a, int U, int nw, hipStream_t st) {
   switch (U) {
-    case 8: return launch(admm_ul_f32<8, 0, 0, 3>, a, nw, st);
+    case 8: return launch<8>(admm_ul_f32<8, 0, 0, 3>, a, nw, st);
     case 16: return launch_resident<16, 3>(a, nw, st);
     case 32: return launch_resident<32, 3>(a, nw, st);
     case 64: return launch_resident<64, 3>(a, nw, st);
@@ -3687,25 +3716,34 @@ hipError_t launch_pack_h16(const c32* H, uint32_t* H16, float* hscale, int n_sc,
   const size_t tiles = (size_t)n_sc * C;
   if (tiles == 0) return hipSuccess;
   if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(pack_h16, dim3((unsigned)tiles), dim3(256), 0, st, H, H16, hscale, B, U, C);
+  const size_t most = (size_t)most_blocks(256) / C;   // subcarriers per launch
+  for (size_t k = 0; k < (size_t)n_sc; k += most) {
+    const size_t n = (size_t)n_sc - k < most ? (size_t)n_sc - k : most;
+    hipLaunchKernelGGL(pack_h16, dim3((unsigned)(n * C)), dim3(256), 0, st, H + k * B * U, H16 + k * B * U,
+                       hscale + k * C, B, U, C);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_scan_nonfinite(const float* x, size_t floats_per_sc, int n_sc, int32_t* status,
                                  hipStream_t st) {
   if (n_sc == 0) return hipSuccess;
-  hipLaunchKernelGGL(scan_nonfinite, dim3((unsigned)n_sc), dim3(256), 0, st, x, floats_per_sc, status);
+  for (long k = 0; k < n_sc; k += most_blocks(256)) {
+    const long n = n_sc - k < most_blocks(256) ? n_sc - k : most_blocks(256);
+    hipLaunchKernelGGL(scan_nonfinite, dim3((unsigned)n), dim3(256), 0, st, x + k * floats_per_sc, floats_per_sc,
+                       status + k);
+  }
   return hipGetLastError();
 }
 
 template <int U>
 static hipError_t launch_dcg(const UlArgs& a, int nw, hipStream_t st) {
-  return symbol_columns(U, a.n_sym, a.B, a.S, a.C) ? launch(dcg_ul_f32<U, true>, a, nw, st) : launch(dcg_ul_f32<U>, a, nw, st);
+  return symbol_columns(U, a.n_sym, a.B, a.S, a.C) ? launch<U>(dcg_ul_f32<U, true>, a, nw, st) : launch<U>(dcg_ul_f32<U>, a, nw, st);
 }
 
 hipError_t launch_dcg_ul_f32(const UlArgs& a, int U, int nw, hipStream_t st) {
   switch (U) {
-    case 8: return launch(dcg_ul_f32<8>, a, nw, st);
+    case 8: return launch<8>(dcg_ul_f32<8>, a, nw, st);
     case 16: return launch_dcg<16>(a, nw, st);
     case 32: return launch_dcg<32>(a, nw, st);
     case 64: return launch_dcg<64>(a, nw, st);
@@ -3717,23 +3755,23 @@ template <bool BUDGET>
 static hipError_t launch_dl(const DlArgs& a, int U, int nw, hipStream_t st) {
   const int S = a.S;
   switch (U) {
-    case 8: return launch(admm_dl_f32<8, 8, BUDGET>, a, nw, st);
+    case 8: return launch<8>(admm_dl_f32<8, 8, BUDGET>, a, nw, st);
     case 16:
-      return S <= 8 ? launch(admm_dl_f32<16, 8, BUDGET>, a, nw, st) : launch(admm_dl_f32<16, 16, BUDGET>, a, nw, st);
+      return S <= 8 ? launch<16>(admm_dl_f32<16, 8, BUDGET>, a, nw, st) : launch<16>(admm_dl_f32<16, 16, BUDGET>, a, nw, st);
     case 32:
-      if (S <= 8) return launch(admm_dl_f32<32, 8, BUDGET>, a, nw, st);
+      if (S <= 8) return launch<32>(admm_dl_f32<32, 8, BUDGET>, a, nw, st);
       if (S <= 16) {
         // the budgeted form keeps a second inverse live (176 registers): capped at
         // 128 it spills 152 of them (240 -> 293 us at B=256 C=16, 1200 subcarriers)
-        if constexpr (BUDGET) return launch(admm_dl_f32<32, 16, true>, a, nw, st);
-        return launch(admm_dl_f32_w4<32, 16>, a, nw, st);
+        if constexpr (BUDGET) return launch<32>(admm_dl_f32<32, 16, true>, a, nw, st);
+        return launch<32>(admm_dl_f32_w4<32, 16>, a, nw, st);
       }
-      return launch(admm_dl_f32<32, 32, BUDGET>, a, nw, st);
+      return launch<32>(admm_dl_f32<32, 32, BUDGET>, a, nw, st);
     case 64:
-      if (S <= 8) return launch(admm_dl_f32<64, 8, BUDGET>, a, nw, st);
-      if (S <= 16) return launch(admm_dl_f32<64, 16, BUDGET>, a, nw, st);
-      if (S <= 32) return launch(admm_dl_f32<64, 32, BUDGET>, a, nw, st);
-      return launch(admm_dl_f32<64, 64, BUDGET>, a, nw, st);
+      if (S <= 8) return launch<64>(admm_dl_f32<64, 8, BUDGET>, a, nw, st);
+      if (S <= 16) return launch<64>(admm_dl_f32<64, 16, BUDGET>, a, nw, st);
+      if (S <= 32) return launch<64>(admm_dl_f32<64, 32, BUDGET>, a, nw, st);
+      return launch<64>(admm_dl_f32<64, 64, BUDGET>, a, nw, st);
   }
   return hipErrorInvalidValue;
 }
