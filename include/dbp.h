@@ -290,8 +290,9 @@ int dbp_detect_cg(const void* H, const void* y, void* x_hat, uint8_t* hard,
  *          IV-B solved exactly under ||x_c||^2 <= P_c (problem P0 with the
  *          budgets added as constraints; the unconstrained step when it fits
  *          the budget, else the minimiser on the budget sphere through the
- *          Lagrange multiplier, found by Newton's method on the shifted
- *          regularised Gram), and beta = 1.  Ignored without P_cluster.
+ *          Lagrange multiplier, the root of the step's norm in the shift of
+ *          the regularised Gram), and beta = 1.  Every symbol's result is
+ *          independent of the others'.  Ignored without P_cluster.
  *   T      number of x-updates (T - 1 consensus steps), T >= 1
  *   eps    radius of the precoding constraint ||s - H^d x|| <= eps of
  *          problem P0 (Section IV-A), eps >= 0.  eps = 0 is Algorithm 3 as
@@ -311,7 +312,8 @@ int dbp_precode_admm(const void* H, int h_layout, const void* s, void* x, float*
 /* Uneven batches in one launch: up to DBP_MAX_BATCH frames of ADMM
  * detection (Algorithm 1, FP32) that share U but may differ in every other
  * shape and parameter (n_sc, n_sym, B, C, T, regulariser, QAM, rho, N0) run
- * in one launch over all their subcarriers, followed by one FP64
+ * in one launch over all their subcarriers (several above 2^32 work items),
+ * followed by one FP64
  * re-slice pass over the frames with hard decisions.  Each dbp_frame holds
  * what dbp_detect_admm takes for one frame (device pointers, caller-owned;
  * workspace as there, needed with hard decisions).  Results are

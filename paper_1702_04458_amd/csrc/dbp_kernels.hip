@@ -3761,8 +3761,9 @@ static hipError_t launch_dl(const DlArgs& a, int U, int nw, hipStream_t st) {
     case 32:
       if (S <= 8) return launch<32>(admm_dl_f32<32, 8, BUDGET>, a, nw, st);
       if (S <= 16) {
-        // the budgeted form keeps a second inverse live (176 registers): capped at
-        // 128 it spills 152 of them (240 -> 293 us at B=256 C=16, 1200 subcarriers)
+        // the budgeted form keeps a second inverse live (165 registers, three waves
+        // per SIMD): capped at 128 an earlier build of it spilled 152 (240 -> 293 us
+        // at B=256 C=16, 1200 subcarriers)
         if constexpr (BUDGET) return launch<32>(admm_dl_f32<32, 16, true>, a, nw, st);
         return launch<32>(admm_dl_f32_w4<32, 16>, a, nw, st);
       }
