@@ -312,9 +312,9 @@ int dbp_precode_admm(const void* H, int h_layout, const void* s, void* x, float*
 /* Uneven batches in one launch: up to DBP_MAX_BATCH frames of ADMM
  * detection (Algorithm 1, FP32) that share U but may differ in every other
  * shape and parameter (n_sc, n_sym, B, C, T, regulariser, QAM, rho, N0) run
- * in one launch over all their subcarriers (several above 2^32 work items),
- * followed by one FP64
- * re-slice pass over the frames with hard decisions.  Each dbp_frame holds
+ * in one launch over all their subcarriers (several launches above 2^32 work
+ * items), followed by one FP64 re-slice pass over the frames with hard
+ * decisions.  Each dbp_frame holds
  * what dbp_detect_admm takes for one frame (device pointers, caller-owned;
  * workspace as there, needed with hard decisions).  Results are
  * bit-identical to dbp_detect_admm on each frame alone.  Frames are

@@ -132,7 +132,7 @@ __host__ __device__ inline bool symbol_columns(int U, int n_sym, int B, int S, i
   return U >= 16 && n_sym >= (U == 16 ? 4 : U == 32 ? 5 : T > 8 && C > 1 ? 4 : 3) && C > 32 / U && 8 * (int64_t)S * U <= most &&
          8 * (7 * (int64_t)B + S) <= most;
 }
-// one launch of grid workgroups (nw waves each; the sum of the frames' blocks) over all frames of b
+// all frames of b: grid workgroups of nw waves (the sum of the frames' blocks), in one launch below 2^32 work items
 hipError_t launch_admm_ul_f32_batch(const UlBatch& b, int U, int nw, int grid, hipStream_t st);
 // FP64 re-slice of the flagged subcarriers of every frame of b
 hipError_t launch_admm_ul_fix64_batch(const FixBatch& b, int U, int n_slots, hipStream_t st);
